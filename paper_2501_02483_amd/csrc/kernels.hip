@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <utility>
 
 #include "launch.h"
 #include "stiles_internal.h"
@@ -601,274 +602,258 @@ __device__ __attribute__((noinline)) uint64_t task_trsm(const ExecMat& M, const 
 
 // ------------------------------------------------- diagonal tile: POTRF + TRTRI
 // Blocked right-looking Cholesky of one T x T tile held in LDS, with 16-wide
-// panels.  For each panel the 16 x 16 diagonal block is factored in the
-// registers of wave 0 (diag_block16) and inverted by all four waves
-// (inv_block16), the panel below is solved against the inverse block and
-// the trailing matrix is updated, both as 16 x 16 x 16 MFMA products.  The inverse of the whole factor is built one
-// block row at a time, as soon as its diagonal block is inverted, on the
-// waves the panel leaves idle:
-//   X_ii = D_i^{-1},  X_ib = -D_i^{-1} sum_{b <= q < i} L_iq X_qb.
+// panels, extended by rows of the identity: eliminating the columns of
+// [A; I] leaves [L; L^{-T}], so the inverse costs no step of its own on the
+// chain.  The identity's row block b is zero left of panel b, and L needs no
+// storage right of its diagonal blocks: the strict upper blocks of the tile
+// buffer hold the identity part, and 16 rows below the tile its diagonal
+// blocks D_b^{-T} (D_b the diagonal blocks of L), starting as I.
+//
+// A panel therefore has T - 16 rows besides its diagonal block (those of L
+// below it, those of the identity part above it), and the 16 identity rows:
+// one row per lane of wave 0 at T = 64.  Meanwhile waves 1 to 3 apply the
+// previous panel to the columns beyond this one and store its part of the
+// results; between two panels every wave updates one 16 x 16 block of the
+// next panel's columns on the matrix cores.
+//
+// The chain of 64 pivots on one wave bounds the task; a wave issues about one
+// vector instruction in six cycles, so the panel is written for few of them
+// (about 400 for 16 columns of 80 rows): every 16-lane row holds its own copy
+// of the diagonal block, whose multipliers reach the lanes as DPP operands of
+// the updates.  Measured from the last wait, one workgroup alone: T = 64
+// 27.5 -> 9.5 us, T = 32 11.4 -> 6.0 us against 16 x 16 diagonal blocks
+// factored through LDS with the inverse and the panel as steps of their own
+// (a chain-bound matrix, n = 10,000, w = 64, natural order: 5.98 -> 3.16 ms).
 
-__device__ __forceinline__ double bcast(double v, int lane) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-  return __hiloint2double(hi, lo);
+// acc -= a(lane Q of the 16-lane row) * b; a must not have been written by the
+// two preceding vector instructions
+template <int Q>
+__device__ __forceinline__ void fnma_row(double& acc, double a, double b) {
+  asm("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(a), "v"(b), "n"(Q));
+}
+// value of lane Q of each 16-lane row
+template <int Q>
+__device__ __forceinline__ double row_value(double v) {
+  double d;
+  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(v), "n"(Q));
+  return d;
 }
 
-// broadcast of lane r of every 16-lane row to the whole row (DPP row_newbcast)
-__device__ __forceinline__ int row_bcast32(int v, int r) {
-  switch (r) {
-    case 0: return __builtin_amdgcn_update_dpp(0, v, 0x150, 0xF, 0xF, false);
-    case 1: return __builtin_amdgcn_update_dpp(0, v, 0x151, 0xF, 0xF, false);
-    case 2: return __builtin_amdgcn_update_dpp(0, v, 0x152, 0xF, 0xF, false);
-    case 3: return __builtin_amdgcn_update_dpp(0, v, 0x153, 0xF, 0xF, false);
-    case 4: return __builtin_amdgcn_update_dpp(0, v, 0x154, 0xF, 0xF, false);
-    case 5: return __builtin_amdgcn_update_dpp(0, v, 0x155, 0xF, 0xF, false);
-    case 6: return __builtin_amdgcn_update_dpp(0, v, 0x156, 0xF, 0xF, false);
-    case 7: return __builtin_amdgcn_update_dpp(0, v, 0x157, 0xF, 0xF, false);
-    case 8: return __builtin_amdgcn_update_dpp(0, v, 0x158, 0xF, 0xF, false);
-    case 9: return __builtin_amdgcn_update_dpp(0, v, 0x159, 0xF, 0xF, false);
-    case 10: return __builtin_amdgcn_update_dpp(0, v, 0x15A, 0xF, 0xF, false);
-    case 11: return __builtin_amdgcn_update_dpp(0, v, 0x15B, 0xF, 0xF, false);
-    case 12: return __builtin_amdgcn_update_dpp(0, v, 0x15C, 0xF, 0xF, false);
-    case 13: return __builtin_amdgcn_update_dpp(0, v, 0x15D, 0xF, 0xF, false);
-    case 14: return __builtin_amdgcn_update_dpp(0, v, 0x15E, 0xF, 0xF, false);
-    default: return __builtin_amdgcn_update_dpp(0, v, 0x15F, 0xF, 0xF, false);
-  }
+// Deferred updates of column C: those its successor's pivot does not need,
+// to D[C + 2] .. D[15], then a[C + 1] .. a[15].  Every update of D[q] by
+// column C < q - 1 has been applied when column q - 1 ends.
+constexpr int deferred_count(int c) { return c < 0 ? 0 : 29 - 2 * c; }
+template <int C, int I>
+__device__ __forceinline__ void deferred_update(double (&D)[16], double (&a)[16]) {
+  if constexpr (I < 14 - C) fnma_row<C + 2 + I>(D[C + 2 + I], D[C], D[C]);
+  else fnma_row<2 * C + I - 13>(a[2 * C + I - 13], D[C], a[C]);
+}
+// one of six slots of them, kept in its place by the scheduling barrier
+template <int C, int SLOT>
+__device__ __forceinline__ void deferred_slot(double (&D)[16], double (&a)[16]) {
+  constexpr int lo = deferred_count(C) * SLOT / 6, hi = deferred_count(C) * (SLOT + 1) / 6;
+  [&]<int... I>(std::integer_sequence<int, I...>) {
+    (deferred_update<C, lo + I>(D, a), ...);
+  }(std::make_integer_sequence<int, hi - lo>());
+  __builtin_amdgcn_sched_barrier(0);
 }
 
-__device__ __forceinline__ double row_bcast(double v, int r) {
-  return __hiloint2double(row_bcast32(__double2hiint(v), r), row_bcast32(__double2loint(v), r));
-}
-
-// Cholesky factor of one 16 x 16 diagonal block on one wave.  Lane l holds
-// row i = l & 15 of the columns g + 4 s (g = l >> 4, s = 0..3).  Column j:
-// the pivot is read from its lane, the owner lanes scale the column and
-// publish it through LDS (the operations of one wave reach LDS in order),
-// and every lane applies its part of the rank-1 update.  The published
-// columns (zero above the diagonal) go to pcol (16 columns with leading
-// dimension T), the reciprocal pivots to rinv: the caller passes the upper
-// block (0, T/16 - 1) of the tile buffer, which no other step uses while a
-// diagonal block is factored and inverted.  The wave's issue rate, not the
-// latency of the pivot chain, sets its time, so the inverse is left to all
-// four waves (inv_block16).
-template <int T>
-__device__ __forceinline__ void diag_block16(double* S, double* rinv, double* pcol, int c0, int lane, int& fail) {
-  const int i = lane & 15, g = lane >> 4;
-  double a[4];
-#pragma unroll
-  for (int s = 0; s < 4; s++) a[s] = S[(c0 + i) + (c0 + g + 4 * s) * T];
-  double piv[16];
-  // the pivot of column j + 1 is formed from broadcast values as soon as
-  // L(j + 1, j) exists, ahead of the lane updates that go through LDS
-  double d = bcast(a[0], 0);
-#pragma unroll
-  for (int j = 0; j < 16; j++) {
-    const int gj = j & 3, sj = j >> 2;
-    const double rs = rsqrt_c(d);
-    if (!(d > 0.0) && fail < 0) fail = c0 + j;
-    piv[j] = rs;
-    const double v = i == j ? d * rs : (i > j ? a[sj] * rs : 0.0);
-    if (j < 15) {
-      const int gn = (j + 1) & 3, sn = (j + 1) >> 2;
-      const double pold = bcast(a[sn], (j + 1) + 16 * gn);   // A(j+1, j+1) before column j
-      const double l1 = bcast(v, (j + 1) + 16 * gj);         // L(j+1, j)
-      d = fma(-l1, l1, pold);
-    }
-    if (g == gj) {
-      a[sj] = v;
-      pcol[i + j * T] = v;
-    }
-    __builtin_amdgcn_wave_barrier();
-    const double lij = pcol[i + j * T];
-#pragma unroll
-    for (int s = 0; s < 4; s++) {
-      const int q = g + 4 * s;
-      if (q > j) a[s] = fma(-lij, pcol[q + j * T], a[s]);
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < 4; s++) {
-    const int c = g + 4 * s;
-    if (i >= c) S[(c0 + i) + (c0 + c) * T] = a[s];
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int j = 0; j < 16; j++) rinv[c0 + j] = piv[j];
+// Column J of a panel: d[J] the pivot, D the diagonal block's rows (one per
+// lane of each 16-lane row), a one further row per lane.  The steps of
+// 1/sqrt(d) (rsqrt_c) depend on each other: the previous column's deferred
+// updates go between them.
+template <int J>
+__device__ __forceinline__ void panel_column(double (&D)[16], double (&a)[16], double (&d)[16]) {
+  const double y0 = __builtin_amdgcn_rsq(d[J]);
+  deferred_slot<J - 1, 0>(D, a);
+  const double t = -d[J] * y0;
+  deferred_slot<J - 1, 1>(D, a);
+  const double e = fma(t, y0, 1.0);
+  deferred_slot<J - 1, 2>(D, a);
+  const double h = fma(0.375, e, 0.5), g = y0 * e;
+  deferred_slot<J - 1, 3>(D, a);
+  const double rs = fma(g, h, y0);
+  deferred_slot<J - 1, 4>(D, a);
+  D[J] *= rs;
+  asm("s_nop 1" : "+v"(D[J]));   // the DPP reads of D[J] follow two wait states after its write
+  deferred_slot<J - 1, 5>(D, a);
+  if constexpr (J < 15) {
+    fnma_row<J + 1>(D[J + 1], D[J], D[J]);
+    a[J] *= rs;
+    d[J + 1] = row_value<J + 1>(D[J + 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    panel_column<J + 1>(D, a, d);
+  } else {
+    a[J] *= rs;
   }
 }
 
-// Inverse of a factored 16 x 16 diagonal block (its columns in pcol, the
-// reciprocal pivots in rinv), by all four waves after a barrier: the
-// 16-lane row g of wave w computes column 4 w + g of D^{-1} by forward
-// substitution, each final entry broadcast inside its 16-lane row by DPP.
-template <int T>
-__device__ __forceinline__ void inv_block16(double* Xi, const double* rinv, const double* pcol, int c0, int wave,
-                                            int lane) {
-  const int i = lane & 15, c = 4 * wave + (lane >> 4);
-  double x = i == c ? 1.0 : 0.0;
-#pragma unroll
-  for (int rr = 0; rr < 16; rr++) {
-    const double lir = pcol[i + rr * T];   // L(i, rr)
-    if (i == rr) x *= rinv[c0 + rr];
-    const double xb = row_bcast(x, rr);
-    if (i > rr) x = fma(-lir, xb, x);
-  }
-  if (i >= c) Xi[(c0 + i) + (c0 + c) * T] = x;
-}
-
-template <int T>
-__device__ __forceinline__ void inv_row_block(double* S, double* Xi, int b, int q, int lane) {
-  v4d u = v4d{0.0, 0.0, 0.0, 0.0};
-  for (int p = q; p < b; p++) {
-#pragma unroll
-    for (int kq = 0; kq < 16; kq += 4) {
-      const double av = S[(16 * b + (lane & 15)) + (16 * p + kq + (lane >> 4)) * T];    // L(b, p)
-      const double bv = Xi[(16 * p + kq + (lane >> 4)) + (16 * q + (lane & 15)) * T];   // X(p, q)
-      u = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, u, 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int rr = 0; rr < 4; rr++) S[(16 * q + (lane >> 4) + 4 * rr) + (16 * b + (lane & 15)) * T] = u[rr];
-  __builtin_amdgcn_wave_barrier();
-  v4d xv = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kq = 0; kq < 16; kq += 4) {
-    const double av = Xi[(16 * b + (lane & 15)) + (16 * b + kq + (lane >> 4)) * T];   // D_b^{-1}
-    const double bv = S[(16 * q + kq + (lane >> 4)) + (16 * b + (lane & 15)) * T];    // U
-    xv = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, xv, 0, 0, 0);
-  }
-#pragma unroll
-  for (int rr = 0; rr < 4; rr++) Xi[(16 * b + (lane >> 4) + 4 * rr) + (16 * q + (lane & 15)) * T] = -xv[rr];
-}
-
-// POTRF waits for its predecessors itself: with TF_SPLIT it prefetches its
-// tile once the early ones (its update chain) have finished and waits last
-// for the TRSM of its fused operand X = L_(k,k-1) (the panel of the previous
+// POTRF waits for its predecessors itself: with TF_SPLIT it stages its tile
+// once the early ones (its update chain) have finished and waits last for
+// the TRSM of its fused operand X = L_(k,k-1) (the panel of the previous
 // column, on the pivot chain).  Returns the time its last wait ended.
+// S: tile buffer with leading dimension T + 17, Xi: T x T (the fused operand).
 template <int T, int K>
 __device__ __attribute__((noinline)) uint64_t task_potrf(const ExecMat& M, const int32_t* w, double* S, double* Xi,
-                                                         double* rinv, int32_t* cnt, ExecCtrl* ctrl, uint64_t limit,
-                                                         bool& ok) {
-  constexpr int TT = T * T, NBK = T / 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                                         int32_t* cnt, ExecCtrl* ctrl, uint64_t limit, bool& ok) {
+  constexpr int TT = T * T, NBK = T / 16, LD = T + 17;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lk = lane >> 4;
   const bool split = (__builtin_amdgcn_readfirstlane(w[0]) & TF_SPLIT) != 0;
   if (ok) ok = wait_below(cnt, split ? MERGED_FDEP : 1, ctrl, limit);
   if (!ok) return 0;
   uint64_t t_start = M.trace ? wall_clock64() : 0;
   double* C = M.tiles + (int64_t)w[1] * TT;
   const int k = w[2];
+  // the fused update with column k-1, C_kk -= X X^T, is applied block by
+  // block: the first block column before the first panel, the rest by waves
+  // 1 to 3 during the first two panels
+  const bool fused = __builtin_amdgcn_readfirstlane((int)(w[4] > w[3])) != 0;
   {
-    // C is prefetched; the fused operand X = L_(k,k-1) follows the last wait
-    const bool fused = w[4] > w[3];
     const int64_t xt = fused ? __builtin_amdgcn_readfirstlane(M.pairs[2 * w[3]]) : 0;
-    TileStage<T, double> st, sx;
+    TileStage<T, double> st;
     st.load(C);
+#pragma unroll
+    for (int q = 0; q < T * 16 / NT; q++) {
+      const int e = tid + q * NT;
+      S[T + (e & 15) + (e >> 4) * LD] = (e & 15) == ((e >> 4) & 15) ? 1.0 : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < TileStage<T, double>::NV; q++) {
+      const int e = 2 * (tid + q * NT);
+      S[(e % T) + (e / T) * LD] = st.r[q].x;
+      S[(e % T) + (e / T) * LD + 1] = st.r[q].y;
+    }
     if (split) {
       ok = wait_below(cnt, 1, ctrl, limit);
       if (!ok) return 0;
       if (M.trace) t_start = wall_clock64();
     }
-    if (fused) sx.load(M.tiles + xt * TT);
-    st.store(S);
     if (fused) {
-      // fused update with column k-1: C_kk -= X X^T
-      constexpr int W = T / 2, NB = T / 32;
-      const int r0 = (wave >> 1) * W, c0 = (wave & 1) * W;
-      sx.store(Xi);
-      __syncthreads();
-      v4d acc[NB][NB];
-#pragma unroll
-      for (int i = 0; i < NB; i++)
-#pragma unroll
-        for (int j = 0; j < NB; j++) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-      mma_f64<T>(acc, Xi, Xi, r0, c0, lane);
-#pragma unroll
-      for (int i = 0; i < NB; i++)
-#pragma unroll
-        for (int j = 0; j < NB; j++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-            S[row + col * T] -= acc[i][j][r];
-          }
-      __syncthreads();
+      st.load(M.tiles + xt * TT);
+      st.store(Xi);
     }
   }
-  for (int e = tid; e < TT; e += NT) Xi[e] = 0.0;
   __syncthreads();
-  int fail = -1;
-  double* pcol = S + (T - 16) * T;   // upper block (0, T/16 - 1), unused by the factorization
-  if (tid < 64) diag_block16<T>(S, rinv, pcol, 0, lane, fail);
-#pragma unroll 1
-  for (int b = 0; b < NBK; b++) {
-    const int c0 = 16 * b;
-    __syncthreads();   // diagonal block b factored, trailing updates of step b-1 done
-    inv_block16<T>(Xi, rinv, pcol, c0, wave, lane);
-    __syncthreads();   // D_b^{-1} complete
-    // ---- row block b of the inverse, X(b, q) for q < b, on the waves that
-    //      the panel below leaves idle (every input is final by now)
-    {
-      const int q = wave - (NBK - 1 - b);
-      if (q >= 0 && q < b) inv_row_block<T>(S, Xi, b, q, lane);
+  // sum of the fused update for block (r, c): 16 rows from each of X's row
+  // blocks r and c, two accumulation chains
+  auto fused_sum = [&](int r, int c) {
+    v4d u0 = v4d{0.0, 0.0, 0.0, 0.0}, u1 = v4d{0.0, 0.0, 0.0, 0.0};
+    const double* xr = Xi + 16 * r + li + lk * T;
+    const double* xc = Xi + 16 * c + li + lk * T;
+#pragma unroll
+    for (int kq = 0; kq < T; kq += 8) {
+      u0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xc[kq * T], xr[kq * T], u0, 0, 0, 0);
+      u1 = __builtin_amdgcn_mfma_f64_16x16x4f64(xc[(kq + 4) * T], xr[(kq + 4) * T], u1, 0, 0, 0);
     }
-    if (b + 1 == NBK) __syncthreads();
-    if (b + 1 < NBK) {
-      // ---- panel: L(R, c0:c0+16) = A(R, c0:c0+16) D^{-T}, R = rows below (MFMA)
-      //      one 16-row block per wave
-      const int nrb = NBK - 1 - b;
-      v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
-      const int rb = c0 + 16 + 16 * wave;
-      if (wave < nrb) {
-        // D^{-T}(l, j) = Dinv(j, l): B(l, j) at Xi[(c0 + j) + (c0 + l) * T] -> ldb swap
-        const double* A = S + rb + c0 * T;
+    return u0 + u1;
+  };
+  // block (r, c) -= u
+  auto subtract = [&](int r, int c, v4d u) {
+    double* o = S + 16 * r + li + (16 * c + lk) * LD;
 #pragma unroll
-        for (int kq = 0; kq < 16; kq += 4) {
-          const double av = A[(lane & 15) + (kq + (lane >> 4)) * T];
-          const double bv = Xi[(c0 + (lane & 15)) + (c0 + kq + (lane >> 4)) * T];
-          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+    for (int q = 0; q < 4; q++) o[4 * q * LD] -= u[q];
+  };
+  // block (r, c) after panel p, u + P_r P_c^T off: rows of L (r >= c) or of
+  // the identity part (r <= p; its row block p is still on the rows below
+  // the tile, and starts from zero here)
+  auto apply = [&](int r, int c, int p, v4d u) {
+    const double* Q = S + 16 * c + li + (16 * p + lk) * LD;
+    const double* P = S + 16 * (r == p ? NBK : r) + li + (16 * p + lk) * LD;
+    double* o = S + 16 * r + li + (16 * c + lk) * LD;
+    double old[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const double v = o[4 * q * LD];
+      old[q] = r == p ? 0.0 : v;
+    }
+#pragma unroll
+    for (int kq = 0; kq < 16; kq += 4)
+      u = __builtin_amdgcn_mfma_f64_16x16x4f64(Q[kq * LD], P[kq * LD], u, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; q++) o[4 * q * LD] = old[q] - u[q];
+  };
+  // stores of panel p by the threads t0 + step i: its columns of L, and its
+  // rows of L^{-1}, the transpose of the identity part
+  GLOBAL double* Cg = gp(C);
+  GLOBAL double* Lg = gp(M.linv + (int64_t)k * TT);
+  auto store_panel = [&](int p, int t0, int step) {
+#pragma unroll 4
+    for (int e = t0; e < 16 * T; e += step) {
+      const int row = e % T, col = 16 * p + e / T;
+      const double v = S[row + col * LD];
+      st_dev(Cg + row + col * T, row >= col ? v : 0.0);
+      const int xr = 16 * p + (e & 15), xc = e >> 4;
+      const double x = S[((xr ^ xc) < 16 ? T + (xc & 15) : xc) + xr * LD];
+      st_dev(Lg + xr + xc * T, xr >= xc ? x : 0.0);
+    }
+  };
+  const v4d zero = v4d{0.0, 0.0, 0.0, 0.0};
+  if (fused) {
+    if (wave < NBK) subtract(wave, 0, fused_sum(wave, 0));
+    __syncthreads();
+  }
+  int fail = -1;
+#pragma unroll 1
+  for (int p = 0; p < NBK; p++) {
+    const int c0 = 16 * p;
+    if (wave == 0) {
+      // row of this lane: the rows of L below the diagonal block, those of
+      // the identity part above it, the 16 rows below the tile
+      const int l = lane & (T - 1);
+      double* row = S + (l < T - 16 ? (c0 + 16 + l) & (T - 1) : l + 16) + c0 * LD;
+      double* dia = S + c0 + li + c0 * LD;
+      double D[16], a[16];
+#pragma unroll
+      for (int j = 0; j < 16; j++) D[j] = dia[j * LD];
+#pragma unroll
+      for (int j = 0; j < 16; j++) a[j] = row[j * LD];
+      double d[16];
+      d[0] = row_value<0>(D[0]);
+      panel_column<0>(D, a, d);
+#pragma unroll
+      for (int j = 0; j < 16; j++) {
+        dia[j * LD] = D[j];
+        row[j * LD] = a[j];
+      }
+      // a pivot that is not positive makes every later one NaN or negative
+      if (__ballot(!(d[15] > 0.0)) != 0 && fail < 0) {
+#pragma unroll
+        for (int j = 15; j >= 0; j--)
+          if (!(d[j] > 0.0)) fail = c0 + j;
+      }
+    } else if (p == 0) {
+      // the fused update of block column 1 (and, at T = 64, of block (2, 2))
+      if (fused) {
+        for (int q = wave - 1; q < (NBK == 4 ? 4 : 1); q += 3) {
+          const int c = q < 3 ? 1 : 2;
+          subtract(q < 3 ? 1 + q : 2, c, fused_sum(q < 3 ? 1 + q : 2, c));
         }
       }
-      __syncthreads();
-      if (wave < nrb) {
-#pragma unroll
-        for (int q = 0; q < 4; q++) S[(rb + (lane >> 4) + 4 * q) + (c0 + (lane & 15)) * T] = acc[q];
-      }
-      __syncthreads();
-      // ---- trailing update A22 -= P P^T over lower 16 x 16 blocks (MFMA).
-      //      Lookahead: wave 0 updates the next diagonal block (block 0 of
-      //      the trailing matrix) and factors it at once; waves 1..3 update
-      //      the other blocks meanwhile (disjoint LDS regions)
-      const int nb2 = nrb * (nrb + 1) / 2;
-      const int q0 = wave, qstep = wave == 0 ? nb2 : NT / 64 - 1;
-      for (int q = q0; q < nb2; q += qstep) {
-        int bi = 0, rem = q;
-        while (rem > bi) { rem -= bi + 1; bi++; }
-        const int bj = rem;   // bj <= bi
-        const int gi = c0 + 16 + 16 * bi, gj = c0 + 16 + 16 * bj;
-        v4d u = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int kq = 0; kq < 16; kq += 4) {
-          const double av = S[(gi + (lane & 15)) + (c0 + kq + (lane >> 4)) * T];   // P(gi + i, l)
-          const double bv = S[(gj + (lane & 15)) + (c0 + kq + (lane >> 4)) * T];   // P(gj + j, l)
-          u = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, u, 0, 0, 0);
+    } else {
+      // the previous panel's update of the block columns beyond this panel
+      // (at p == 1 with the rest of the fused update, blocks (3, 2), (3, 3));
+      // once there is little of that, the stores of the finished panels
+      int q = 0;
+      for (int r = NBK - 1; r >= 0; r--)
+        for (int c = p + 1; c < NBK; c++) {
+          if (r < c && r >= p) continue;
+          if (q++ % 3 != wave - 1) continue;
+          apply(r, c, p - 1, p == 1 && fused && r == 3 ? fused_sum(r, c) : zero);
         }
-#pragma unroll
-        for (int rr = 0; rr < 4; rr++) S[(gi + (lane >> 4) + 4 * rr) + (gj + (lane & 15)) * T] -= u[rr];
-      }
-      if (tid < 64) {
-        __builtin_amdgcn_wave_barrier();
-        diag_block16<T>(S, rinv, pcol, c0 + 16, lane, fail);
-      }
+      for (int b = p < 2 ? 0 : p - 2; b < (p + 1 == NBK ? p : p - 1); b++) store_panel(b, tid - 64, NT - 64);
+    }
+    __syncthreads();
+    if (p + 1 < NBK) {
+      // the next panel's block column: rows p+1 .. of L, then 0 .. p of the
+      // identity part, one block per wave
+      if (wave < NBK) apply((p + 1 + wave) % NBK, p + 1, p, zero);
+      __syncthreads();
     }
   }
   if (tid == 0 && fail >= 0) atomicMin(M.info, (unsigned long long)(M.row_base[k] + fail + 1));
-  double* Li = M.linv + (int64_t)k * TT;
-  for (int e = tid; e < TT; e += NT) {
-    const int row = e % T, col = e / T;
-    st_dev(C + e, row >= col ? S[e] : 0.0);
-    st_dev(Li + e, Xi[e]);
-  }
+  store_panel(NBK - 1, tid, NT);
   return t_start;
 }
 
@@ -1473,17 +1458,14 @@ __device__ __attribute__((noinline)) void task_tsum(const ExecMat& M, const int3
 // TRSM), triangular-solve tasks, or selected-inversion tasks; they are
 // separate kernels so that each carries only its own code.
 template <int T, int KIND>
-__global__ __launch_bounds__(NT, 2) void exec_kernel(const ExecMat* __restrict__ mats, const int32_t* __restrict__ order,
+__global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat* __restrict__ mats, const int32_t* __restrict__ order,
                                                   int32_t total, ExecCtrl* ctrl, int nrhs, uint64_t limit) {
   constexpr bool SOLVE = KIND == EXEC_SOLVE, SELINV = KIND == EXEC_SELINV, BOTH = KIND == EXEC_FACTOR_SOLVE;
-  // LDS: factorization tasks use S (tile, ld T+1 room), Xi (T x T) and rinv;
-  // solve tasks only a T x 16 block (Xi in the solve kernel, LI in the
-  // combined factorization + solve kernel); selected-inversion tasks two
-  // padded tiles.
-  __shared__ __attribute__((aligned(16))) double S[SOLVE ? 2 : SELINV ? T * (T + 2) : T * (T + 1)];
+  // LDS: factorization tasks use S (a tile; POTRF: leading dimension T + 17)
+  // and Xi (T x T); solve tasks only a T x 16 block of Xi; selected-inversion
+  // tasks two padded tiles.
+  __shared__ __attribute__((aligned(16))) double S[SOLVE ? 2 : SELINV ? T * (T + 2) : T * (T + 17)];
   __shared__ __attribute__((aligned(16))) double Xi[SOLVE ? T * 16 : SELINV ? T * (T + 2) : T * T];
-  __shared__ double rinv[(KIND == EXEC_FACTOR || BOTH) ? T : 1];
-  __shared__ __attribute__((aligned(16))) double LI[BOTH ? T * 16 : 2];
   __shared__ int32_t s_ticket;
   // Control flow outside the task bodies is kept uniform across the
   // workgroup (values broadcast with readfirstlane, loops with uniform bounds
@@ -1546,7 +1528,7 @@ __global__ __launch_bounds__(NT, 2) void exec_kernel(const ExecMat* __restrict__
       if (type == TK_FSUM) {
         if (ok) task_fsum<T, KIND>(M, w, nrhs);
       } else {
-        t_start = task_solve_r<T, KIND>(M, w, nrhs, cnt, LI, ctrl, limit, ok);
+        t_start = task_solve_r<T, KIND>(M, w, nrhs, cnt, Xi, ctrl, limit, ok);
       }
     } else if (ok) {
       switch (type) {
@@ -1554,7 +1536,7 @@ __global__ __launch_bounds__(NT, 2) void exec_kernel(const ExecMat* __restrict__
         case TK_UPDB: task_update_block<T, KIND>(M, w, S, Xi); break;
         case TK_PART: task_update<T, KIND>(M, w, 1, S, Xi); break;
         case TK_TREE: task_tree<T, KIND>(M, w); break;
-        case TK_POTRF: t_start = task_potrf<T, KIND>(M, w, S, Xi, rinv, cnt, ctrl, limit, ok); break;
+        case TK_POTRF: t_start = task_potrf<T, KIND>(M, w, S, Xi, cnt, ctrl, limit, ok); break;
         default: t_start = task_trsm<T, KIND>(M, w, S, Xi, cnt, ctrl, limit, ok); break;
       }
     }
