@@ -172,11 +172,8 @@ int device_wg_capacity(int T) {
     hipDeviceProp_t prop;
     int cus = 256;
     if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
-    // LDS of the executor: 2 T^2 + 17 T doubles (+ ticket)
-    const size_t lds = (2 * (size_t)T * T + 17 * T) * 8 + 64;
-    int per_cu = (int)std::min<size_t>(8, (160 * 1024) / lds);
-    if (per_cu < 1) per_cu = 1;
-    c = cus * per_cu;
+    // resident workgroups of the executor per CU (its launch bounds and LDS)
+    c = cus * (T == 64 ? 2 : 3);
   }
   return c;
 }

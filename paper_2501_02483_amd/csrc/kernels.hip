@@ -77,6 +77,12 @@ __device__ __forceinline__ void st_dev(GLOBAL float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_dev(double* p, double v) { st_dev(gp(p), v); }
+// the same for 16 bytes (an atomic store has at most 8); a vector instruction
+// may overwrite the data registers of so wide a store two wait states after it
+typedef double v2d __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void st_dev(GLOBAL v2d* p, v2d v) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
+}
 
 // ------------------------------------------------------------------ helpers
 
@@ -100,91 +106,28 @@ __device__ __forceinline__ double rsqrt_c(double d) {
 }
 
 // ------------------------------------------------------- tile products (MFMA)
-// acc[i][j] covers C rows r0 + 16 j + (lane & 15) and C columns
-// c0 + 16 i + (lane >> 4) + 4 r (FP64 MFMA output layout on gfx950: lane l,
-// register r holds D[(l >> 4) + 4 r][l & 15]).  The A operand is taken from
-// Y (C columns), the B operand from X (C rows), so that the 16 lanes of one
-// row group touch 16 consecutive rows of a column-major tile.  Operands are
-// read from LDS, where a whole tile pair has been staged.
-
-template <int T>
-__device__ __forceinline__ void mma_f64(v4d (&acc)[T / 32][T / 32], const double* X, const double* Y, int r0, int c0,
-                                        int lane) {
-  constexpr int NB = T / 32;
-  const double* xp = X + r0 + (lane & 15) + (lane >> 4) * T;
-  const double* yp = Y + c0 + (lane & 15) + (lane >> 4) * T;
-  // the operands of step k + 4 are read from LDS while step k's MFMAs run
-  double a[NB], b[NB];
-#pragma unroll
-  for (int q = 0; q < NB; q++) {
-    a[q] = yp[q * 16];
-    b[q] = xp[q * 16];
+// 16 x 16 x 4 products: lane l holds A[l & 15][l >> 4], B[l >> 4][l & 15] and,
+// in register r of the result, D[col(l, r)][l & 15].  The A operand is taken
+// from Y (columns of C), the B operand from X (rows of C), so that the 16
+// lanes of one row group touch neighbouring rows of a column-major tile.
+template <typename E>
+struct Mma;
+template <>
+struct Mma<double> {
+  typedef v4d acc_t;
+  static __device__ __forceinline__ v4d mfma(double a, double b, v4d c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
-#pragma unroll
-  for (int k = 0; k < T; k += 4) {
-    double an[NB], bn[NB];
-    if (k + 4 < T) {
-#pragma unroll
-      for (int q = 0; q < NB; q++) {
-        an[q] = yp[q * 16 + (k + 4) * T];
-        bn[q] = xp[q * 16 + (k + 4) * T];
-      }
-    }
-    // keep the next step's LDS reads ahead of this step's MFMAs
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < NB; i++)
-#pragma unroll
-      for (int j = 0; j < NB; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    if (k + 4 < T) {
-#pragma unroll
-      for (int q = 0; q < NB; q++) {
-        a[q] = an[q];
-        b[q] = bn[q];
-      }
-    }
+  static __device__ __forceinline__ int col(int lane, int r) { return (lane >> 4) + 4 * r; }   // result column
+};
+template <>
+struct Mma<float> {
+  typedef v4f acc_t;
+  static __device__ __forceinline__ v4f mfma(float a, float b, v4f c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
-}
-
-// FP32 variant (mixed mode); FP32 MFMA output layout: lane l, register r holds
-// D[4 (l >> 4) + r][l & 15], so acc[i][j][r] covers column c0 + 16 i + 4 (lane >> 4) + r.
-template <int T>
-__device__ __forceinline__ void mma_f32(v4f (&acc)[T / 32][T / 32], const float* X, const float* Y, int r0, int c0,
-                                        int lane) {
-  constexpr int NB = T / 32;
-  const float* xp = X + r0 + (lane & 15) + (lane >> 4) * T;
-  const float* yp = Y + c0 + (lane & 15) + (lane >> 4) * T;
-  // the operands of step k + 4 are read from LDS while step k's MFMAs run
-  float a[NB], b[NB];
-#pragma unroll
-  for (int q = 0; q < NB; q++) {
-    a[q] = yp[q * 16];
-    b[q] = xp[q * 16];
-  }
-#pragma unroll
-  for (int k = 0; k < T; k += 4) {
-    float an[NB], bn[NB];
-    if (k + 4 < T) {
-#pragma unroll
-      for (int q = 0; q < NB; q++) {
-        an[q] = yp[q * 16 + (k + 4) * T];
-        bn[q] = xp[q * 16 + (k + 4) * T];
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < NB; i++)
-#pragma unroll
-      for (int j = 0; j < NB; j++) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    if (k + 4 < T) {
-#pragma unroll
-      for (int q = 0; q < NB; q++) {
-        a[q] = an[q];
-        b[q] = bn[q];
-      }
-    }
-  }
-}
+  static __device__ __forceinline__ int col(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
 
 // Whole-tile staging through registers: every thread moves its share of a
 // T x T tile with 16-byte loads, so a tile arrives after one memory latency
@@ -247,123 +190,213 @@ __device__ __forceinline__ bool wait_below(int32_t* cnt, int32_t bound, ExecCtrl
 }
 
 
+// ---- operand ring of the update products
+// Tile pairs stream through LDS in stages of KS columns of X and of Y (a
+// column range of a column-major tile is contiguous), written by the memory
+// system itself (global_load_lds: no staging registers and no LDS store
+// instructions).  Two or more stages are in flight while one is multiplied;
+// one barrier per stage, after its first step so that the matrix cores work
+// meanwhile, says both that the next stage has arrived and that the slot of
+// the previous one is free.  Tiles staged whole through registers gave the
+// matrix cores nothing to do while a pair was stored to LDS and the next
+// one's 16 loads went out; 512 workgroups of 12-product tasks on tiles in
+// L2: FP64 49 -> 58 TFLOP/s, FP32 96 -> 105; on tiles in HBM both are bound by
+// it (43 -> 44, 87 -> 89).
+template <int T, typename E>
+struct Ring {
+  static constexpr int KS = T == 64 && sizeof(E) == 8 ? 16 : 32;   // columns per stage
+  static constexpr int SPP = T / KS;                               // stages per tile pair
+  static constexpr int HB = T * KS * (int)sizeof(E);               // bytes of one operand's stage
+  static constexpr int NI = 2 * HB / 4096;                         // 1 KB transfers per wave and stage
+  static constexpr int NST = T == 64 ? 4 : 3;                      // slots (64 KB; 48 KB at T = 32)
+  static_assert(NST * 2 * HB <= 65536, "transfers address LDS below 64 KB");
+};
+
+// 1 KB from base + voff (voff per lane) to LDS at lds + 16 lane.  No register
+// is written, so nothing can be overwritten by a transfer in flight; it
+// counts in vmcnt.
+__device__ __forceinline__ void lds_transfer(uint32_t lds, uint32_t voff, const char* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
+
+// waits until at most `n` of this wave's newest transfers (n = 0, NI or 2 NI)
+// are in flight, then for the other waves
+template <int NI>
+__device__ __forceinline__ void ring_barrier(int n) {
+  if (n >= 2 * NI) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(2 * NI) : "memory");
+  else if (n >= NI) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NI) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+}
+
+// acc += sum over the np tile pairs of pv of X_p Y_p^T, this wave's quarter
+// (rows r0, columns c0; none if !active), operands from `tiles`.  Block j of
+// the quarter holds its rows 2 i + j (i = 0..15), block i its columns
+// 2 j + i, so that a lane reads its operands for both blocks as one pair of
+// neighbours: 16-byte LDS reads run at twice the rate of 8-byte ones, and
+// the matrix cores of a lone workgroup wait for them (cycles per FP64 MFMA
+// in a loop of reads and MFMAs: 69 against 81, without reads 64; two
+// workgroups a CU 66 against 72).
+template <int T, typename E>
+__device__ __forceinline__ void ring_products(typename Mma<E>::acc_t (&acc)[T / 32][T / 32], const E* tiles, int pv,
+                                              int np, E* ring, int r0, int c0, bool active) {
+  typedef Ring<T, E> R;
+  constexpr int NB = T / 32, NI = R::NI, NST = R::NST;
+  const int tid = thread_id(), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + 1024 * wave;
+  const uint32_t voff = 1024 * wave + 16 * lane;
+  const int total = np * R::SPP;
+  // transfer i of stage s into its slot
+  const char *xb, *yb;
+  uint32_t dst;
+  auto stage = [&](int s, int slot) {
+    const int p = s / R::SPP;
+    const int64_t part = (int64_t)(s % R::SPP) * R::HB;
+    xb = (const char*)(tiles + (int64_t)word(pv, 2 * p) * T * T) + part;
+    yb = (const char*)(tiles + (int64_t)word(pv, 2 * p + 1) * T * T) + part;
+    dst = lds0 + (uint32_t)slot * 2 * R::HB;
+  };
+  auto transfer = [&](int i) {
+    const int c = 4096 * (i % (NI / 2));
+    if (i < NI / 2) lds_transfer(dst + c, voff + c, xb);
+    else lds_transfer(dst + R::HB + c, voff + c, yb);
+  };
+#pragma unroll
+  for (int s = 0; s < NST - 1; s++)
+    if (s < total) {
+      stage(s, s);
+#pragma unroll
+      for (int i = 0; i < NI; i++) transfer(i);
+    }
+  ring_barrier<NI>((total < NST - 1 ? total : NST - 1) * NI - NI);
+  int slot = 0, wslot = NST - 1;
+  const int xo = r0 + NB * (lane & 15) + (lane >> 4) * T;
+  const int yo = c0 + NB * (lane & 15) + (lane >> 4) * T + R::HB / (int)sizeof(E);
+  typedef E vec __attribute__((ext_vector_type(NB)));
+  constexpr int SLOT = 2 * R::HB / (int)sizeof(E);
+  E a[NB], b[NB];
+  {
+    const vec y = *(const vec*)(ring + yo), x = *(const vec*)(ring + xo);
+#pragma unroll
+    for (int q = 0; q < NB; q++) {
+      a[q] = y[q];
+      b[q] = x[q];
+    }
+  }
+#pragma unroll 1
+  for (int s = 0; s < total; s++) {
+    const E* cur = ring + slot * SLOT;
+    slot = slot + 1 == NST ? 0 : slot + 1;
+    const E* nxt = ring + slot * SLOT;
+    const bool more = s + NST - 1 < total;
+#pragma unroll
+    for (int k = 0; k < R::KS; k += 4) {
+      // the operands of the next step (at the end, of the next stage's first
+      // one) are read from LDS while this step's MFMAs run
+      E an[NB], bn[NB];
+      const E* src = k + 4 < R::KS ? cur + (k + 4) * T : nxt;
+      {
+        const vec y = *(const vec*)(src + yo), x = *(const vec*)(src + xo);
+#pragma unroll
+        for (int q = 0; q < NB; q++) {
+          an[q] = y[q];
+          bn[q] = x[q];
+        }
+      }
+      if (k >= 4 && more) {
+#pragma unroll
+        for (int i = (k / 4 - 1) * NI / (R::KS / 4 - 1); i < (k / 4) * NI / (R::KS / 4 - 1); i++) transfer(i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (active) {
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+          for (int j = 0; j < NB; j++) acc[i][j] = Mma<E>::mfma(a[i], b[j], acc[i][j]);
+      }
+      if (k == 0) {
+        // early in the stage: the next one has arrived, and no wave still
+        // reads the previous one, whose slot takes the next transfers
+        const int last = s + NST - 2 < total ? s + NST - 2 : total - 1;
+        if (s + 1 < total) ring_barrier<NI>((last - (s + 1)) * NI);
+        if (more) stage(s + NST - 1, wslot);
+        wslot = wslot + 1 == NST ? 0 : wslot + 1;
+      }
+#pragma unroll
+      for (int q = 0; q < NB; q++) {
+        a[q] = an[q];
+        b[q] = bn[q];
+      }
+    }
+  }
+}
+
 // UPD / PART: acc = sum_p X_p Y_p^T over a list of tile pairs (at most 32).
-// mode 0: C_t -= acc (UPD), mode 1: P = acc (PART).  LX, LY: LDS tiles.
-template <int T>
-__device__ __forceinline__ void task_update(const ExecMat& M, const Task& w, int mode, double* LX, double* LY) {
+// mode 0: C_t -= acc (UPD), mode 1: P = acc (PART).  E = double on the factor
+// tiles, float on their FP32 copies (mixed mode; the sum is then applied to
+// the FP64 tile).
+template <int T, typename E>
+__device__ __forceinline__ void update_products(const ExecMat& M, const Task& w, int mode, const E* tiles, E* ring) {
   constexpr int TT = T * T, W = T / 2, NB = T / 32;
-  const int lane = thread_id() & 63, wave = thread_id() >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int r0 = wr * W, c0 = wc * W;
+  const int tid = thread_id(), lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r0 = (wave >> 1) * W, c0 = (wave & 1) * W;
   const bool diag = (w[0] & TF_DIAG) != 0;
-  const bool active = !(diag && wc > wr);   // strictly upper quarter of a diagonal tile
-  const int np = w[3] - w[2];
-  // FP32 products in mixed mode: the updates, and the partials of corner
-  // tiles other than the arrow corner (separator rows under adaptable ND);
-  // the arrow corner's partials too in the all-FP32 variant (mixed == 2)
-  const bool mixed = M.mixed && (mode == 0 || M.mixed == 2 || (w[0] & TF_ARROW) == 0);
+  const bool active = !(diag && c0 > r0);   // strictly upper quarter of a diagonal tile
   const bool accum = mode == 1 && (w[0] & TF_ACC) != 0;   // partial chain: P += sum
   GLOBAL double* out = gp(mode == 0 ? M.tiles + (int64_t)w[1] * TT : M.part + (int64_t)w[4] * TT);
-  const int pv = w.pv;
+  // this lane's elements: rows row0 + j, columns col(i, r)
+  const int row0 = r0 + NB * (lane & 15);
+  auto col = [&](int i, int r) { return c0 + NB * Mma<E>::col(lane, r) + i; };
+  typedef double vec __attribute__((ext_vector_type(NB)));
   // the target's current value is needed only at the end: fetch it now
-  double cin[NB][NB][4];
+  vec cin[NB][4];
   if ((mode == 0 || accum) && active) {
 #pragma unroll
     for (int i = 0; i < NB; i++)
 #pragma unroll
-      for (int j = 0; j < NB; j++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const int row = r0 + 16 * j + (lane & 15);
-          const int col = c0 + 16 * i + (mixed ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r);
-          cin[i][j][r] = out[row + col * T];
-        }
+      for (int r = 0; r < 4; r++) cin[i][r] = *(const GLOBAL vec*)(out + row0 + col(i, r) * T);
   }
-  if (!mixed) {
-    const double* tiles = M.tiles;
-    v4d acc[NB][NB];
+  typename Mma<E>::acc_t acc[NB][NB];
 #pragma unroll
-    for (int i = 0; i < NB; i++)
+  for (int i = 0; i < NB; i++)
 #pragma unroll
-      for (int j = 0; j < NB; j++) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-    TileStage<T, double> sx, sy;
-    sx.load(tiles + (int64_t)word(pv, 0) * TT);
-    sy.load(tiles + (int64_t)word(pv, 1) * TT);
-    for (int p = 0; p < np; p++) {
-      __syncthreads();
-      sx.store(LX);
-      sy.store(LY);
-      __syncthreads();
-      if (p + 1 < np) {
-        sx.load(tiles + (int64_t)word(pv, 2 * p + 2) * TT);
-        sy.load(tiles + (int64_t)word(pv, 2 * p + 3) * TT);
+    for (int j = 0; j < NB; j++) acc[i][j] = typename Mma<E>::acc_t{0, 0, 0, 0};
+  ring_products<T, E>(acc, tiles, w.pv, w[3] - w[2], ring, r0, c0, active);
+  if (!active && mode == 0) return;
+#pragma unroll
+  for (int i = 0; i < NB; i++)
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      vec v;
+#pragma unroll
+      for (int j = 0; j < NB; j++) {
+        const double x = (double)acc[i][j][r];
+        // above the diagonal the target keeps its value; an inactive
+        // quarter's zeros keep a partial fully defined
+        if (mode == 0) v[j] = !diag || row0 + j >= col(i, r) ? cin[i][r][j] - x : cin[i][r][j];
+        else v[j] = accum && active ? cin[i][r][j] + x : x;
       }
-      if (active) mma_f64<T>(acc, LX, LY, r0, c0, lane);
+      GLOBAL double* o = out + row0 + col(i, r) * T;
+      if constexpr (NB == 2) st_dev((GLOBAL v2d*)o, v2d{v[0], v[NB - 1]});
+      else st_dev(o, v[0]);
     }
-    if (active) {
-#pragma unroll
-      for (int i = 0; i < NB; i++)
-#pragma unroll
-        for (int j = 0; j < NB; j++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-            if (mode == 0) {
-              if (!diag || row >= col) st_dev(out + row + col * T, cin[i][j][r] - acc[i][j][r]);
-            } else {
-              st_dev(out + row + col * T, accum ? cin[i][j][r] + acc[i][j][r] : acc[i][j][r]);
-            }
-          }
-    } else if (mode == 1) {   // keep the partial fully defined
-#pragma unroll
-      for (int i = 0; i < NB; i++)
-#pragma unroll
-        for (int j = 0; j < NB; j++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-            st_dev(out + row + col * T, 0.0);
-          }
-    }
-  } else {
-    const float* shadow = M.shadow;
-    float* FX = reinterpret_cast<float*>(LX);
-    float* FY = reinterpret_cast<float*>(LY);
-    v4f acc[NB][NB];
-#pragma unroll
-    for (int i = 0; i < NB; i++)
-#pragma unroll
-      for (int j = 0; j < NB; j++) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-    TileStage<T, float> sx, sy;
-    sx.load(shadow + (int64_t)word(pv, 0) * TT);
-    sy.load(shadow + (int64_t)word(pv, 1) * TT);
-    for (int p = 0; p < np; p++) {
-      __syncthreads();
-      sx.store(FX);
-      sy.store(FY);
-      __syncthreads();
-      if (p + 1 < np) {
-        sx.load(shadow + (int64_t)word(pv, 2 * p + 2) * TT);
-        sy.load(shadow + (int64_t)word(pv, 2 * p + 3) * TT);
-      }
-      if (active) mma_f32<T>(acc, FX, FY, r0, c0, lane);
-    }
-    if (active) {
-#pragma unroll
-      for (int i = 0; i < NB; i++)
-#pragma unroll
-        for (int j = 0; j < NB; j++)
-#pragma unroll
-          for (int r = 0; r < 4; r++) {
-            const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + 4 * (lane >> 4) + r;
-            if (mode == 0) {
-              if (!diag || row >= col) st_dev(out + row + col * T, cin[i][j][r] - (double)acc[i][j][r]);
-            } else {
-              st_dev(out + row + col * T, accum ? cin[i][j][r] + (double)acc[i][j][r] : (double)acc[i][j][r]);
-            }
-          }
-    }
-  }
+}
+
+template <int T>
+__device__ __forceinline__ void task_update(const ExecMat& M, const Task& w, int mode, double* ring) {
+  // FP32 products in mixed mode: the updates, and the partials of corner
+  // tiles other than the arrow corner (separator rows under adaptable ND);
+  // the arrow corner's partials too in the all-FP32 variant (mixed == 2)
+  if (M.mixed && (mode == 0 || M.mixed == 2 || (w[0] & TF_ARROW) == 0))
+    update_products<T, float>(M, w, mode, M.shadow, reinterpret_cast<float*>(ring));
+  else
+    update_products<T, double>(M, w, mode, M.tiles, ring);
 }
 
 // UPDB: a 2 x 2 block of update targets C_(r,c) -= sum_j L_(r,j) L_(c,j)^T,
@@ -380,29 +413,8 @@ __device__ __forceinline__ void task_update(const ExecMat& M, const Task& w, int
 // the FP64 factor tiles, float on the FP32 copies in mixed mode (the
 // product is then subtracted from the FP64 tile).
 template <int T, typename E>
-struct BlockOps;
-template <int T>
-struct BlockOps<T, double> {
-  typedef v4d acc_t;
-  static __device__ __forceinline__ v4d mfma(double a, double b, v4d c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int col(int lane, int r) { return (lane >> 4) + 4 * r; }
-  static __device__ __forceinline__ const double* src(const ExecMat& M) { return M.tiles; }
-};
-template <int T>
-struct BlockOps<T, float> {
-  typedef v4f acc_t;
-  static __device__ __forceinline__ v4f mfma(float a, float b, v4f c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int col(int lane, int r) { return 4 * (lane >> 4) + r; }
-  static __device__ __forceinline__ const float* src(const ExecMat& M) { return M.shadow; }
-};
-
-template <int T, typename E>
-__device__ __forceinline__ void update_block(const ExecMat& M, const Task& w, double* LXd, double* LYd) {
-  typedef BlockOps<T, E> O;
+__device__ __forceinline__ void update_block(const ExecMat& M, const Task& w, const E* tiles, double* LXd, double* LYd) {
+  typedef Mma<E> O;
   typedef typename O::acc_t acc_t;
   typedef E vec __attribute__((ext_vector_type(16 / sizeof(E))));
   constexpr int TT = T * T, H = T / 2, HE = T * H, NB = T / 16;
@@ -418,7 +430,6 @@ __device__ __forceinline__ void update_block(const ExecMat& M, const Task& w, do
   const bool active = tgt >= 0;
   const bool tdiag = dg && wave != 1;
   const int xs = wave & 1, ys = wave >> 1;
-  const E* tiles = O::src(M);
   // staged halves: the Y tiles (k, j), (k+1, j), then (non-diagonal block)
   // the X tiles (ra, j), (rb, j)
   const int nst = dg ? 2 : 4;
@@ -510,15 +521,15 @@ __device__ __forceinline__ void update_block(const ExecMat& M, const Task& w, do
 // The one task body that is a function: it needs nearly every register, and
 // blocks are off by default.  M stays in global memory for it (a descriptor
 // whose address is taken would live in scratch memory).
-template <int T>
+template <int T, int K>   // K: a copy for every kernel kind, not one compiled for all
 __device__ __attribute__((noinline)) void task_update_block(const ExecMat* M, int w0, int nj, int pv, double* LX,
                                                             double* LY) {
   Task w;
   w.w[0] = __builtin_amdgcn_readfirstlane(w0);
   w.w[3] = __builtin_amdgcn_readfirstlane(nj);
   w.pv = pv;
-  if (M->mixed) update_block<T, float>(*M, w, LX, LY);
-  else update_block<T, double>(*M, w, LX, LY);
+  if (M->mixed) update_block<T, float>(*M, w, M->shadow, LX, LY);
+  else update_block<T, double>(*M, w, M->tiles, LX, LY);
 }
 
 // TREE: P_c = P_a + P_b, or C_t -= P_a (+ P_b) at the root (Alg. 3 GEADD).
@@ -1149,7 +1160,8 @@ __device__ __forceinline__ void task_fsum(const ExecMat& M, const Task& w, int n
 // on tiles staged in LDS with leading dimension LP = T + 2: reading a
 // column-major tile directly or transposed is then free of bank conflicts
 // within each group of 16 lanes, and the 16-byte staging stores stay aligned.
-// Output layout as in mma_f64 (each wave owns one (T/2) x (T/2) quarter).
+// Each wave owns one (T/2) x (T/2) quarter: acc[i][j] covers its rows
+// 16 j + (lane & 15) and columns 16 i + (lane >> 4) + 4 r.
 
 template <int T>
 struct PadStage {
@@ -1552,10 +1564,13 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
                                                   int32_t total, ExecCtrl* ctrl, int nrhs, uint64_t limit) {
   constexpr bool SOLVE = KIND == EXEC_SOLVE, SELINV = KIND == EXEC_SELINV, BOTH = KIND == EXEC_FACTOR_SOLVE;
   // LDS: factorization tasks use S (a tile; POTRF: leading dimension T + 17)
-  // and Xi (T x T); solve tasks only a T x 16 block of Xi; selected-inversion
-  // tasks two padded tiles.
-  __shared__ __attribute__((aligned(16))) double S[SOLVE ? 2 : SELINV ? T * (T + 2) : T * (T + 17)];
-  __shared__ __attribute__((aligned(16))) double Xi[SOLVE ? T * 16 : SELINV ? T * (T + 2) : T * T];
+  // and Xi (T x T) or, updates, the whole as a ring; solve tasks only a
+  // T x 16 block of Xi; selected-inversion tasks two padded tiles.
+  constexpr int NS = SOLVE ? 2 : SELINV ? T * (T + 2) : T * (T + 17);
+  constexpr int NX = SOLVE ? T * 16 : SELINV ? T * (T + 2) : T * T;
+  constexpr int NR = SOLVE || SELINV ? 0 : Ring<T, double>::NST * 2 * Ring<T, double>::HB / 8;
+  __shared__ __attribute__((aligned(1024))) double S[NS + NX > NR ? NS + NX : NR];
+  double* const Xi = S + NS;
   __shared__ int32_t s_ticket;
   // Control flow outside the task bodies is kept uniform across the
   // workgroup (values broadcast with readfirstlane, loops with uniform bounds
@@ -1631,9 +1646,9 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
       }
     } else if (ok) {
       switch (type) {
-        case TK_UPD: task_update<T>(M, w, 0, S, Xi); break;
-        case TK_UPDB: task_update_block<T>(mats + mi, w[0], w[3], w.pv, S, Xi); break;
-        case TK_PART: task_update<T>(M, w, 1, S, Xi); break;
+        case TK_UPD: task_update<T>(M, w, 0, S); break;
+        case TK_UPDB: task_update_block<T, KIND>(mats + mi, w[0], w[3], w.pv, S, Xi); break;
+        case TK_PART: task_update<T>(M, w, 1, S); break;
         case TK_TREE: task_tree<T>(M, w); break;
         case TK_POTRF: t_start = task_potrf<T>(M, w, S, Xi, cnt, ctrl, limit, ok); break;
         default: t_start = task_trsm<T>(M, w, S, Xi, cnt, ctrl, limit, ok); break;
