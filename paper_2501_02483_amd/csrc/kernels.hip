@@ -77,12 +77,26 @@ __device__ __forceinline__ void st_dev(GLOBAL float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_dev(double* p, double v) { st_dev(gp(p), v); }
-// the same for 16 bytes (an atomic store has at most 8); a vector instruction
-// may overwrite the data registers of so wide a store two wait states after it
+// The same for 16 bytes of a tile (an atomic store has at most 8): a buffer
+// store, whose cache policy is an operand.  As inline asm the compiler would
+// not count it, and a later wait for loads issued before it would wait for
+// the store too.
 typedef double v2d __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void st_dev(GLOBAL v2d* p, v2d v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(p), "v"(v) : "memory");
-}
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+template <int T>
+struct DevTile {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ explicit DevTile(double* tile)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(tile, 0, T * T * 8, 0x00020000)) {}
+  // element e and the next one, e even
+  __device__ __forceinline__ void store(int e, v2d v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rsrc, 8 * e, 0, /* sc1 */ 16);
+  }
+  __device__ __forceinline__ void store(int e, double v) const {
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), rsrc, 8 * e, 0, /* sc1 */ 16);
+  }
+};
 
 // ------------------------------------------------------------------ helpers
 
@@ -349,7 +363,9 @@ __device__ __forceinline__ void update_products(const ExecMat& M, const Task& w,
   const bool diag = (w[0] & TF_DIAG) != 0;
   const bool active = !(diag && c0 > r0);   // strictly upper quarter of a diagonal tile
   const bool accum = mode == 1 && (w[0] & TF_ACC) != 0;   // partial chain: P += sum
-  GLOBAL double* out = gp(mode == 0 ? M.tiles + (int64_t)w[1] * TT : M.part + (int64_t)w[4] * TT);
+  double* const tile = mode == 0 ? M.tiles + (int64_t)w[1] * TT : M.part + (int64_t)w[4] * TT;
+  const GLOBAL double* out = gp(tile);
+  const DevTile<T> dev(tile);
   // this lane's elements: rows row0 + j, columns col(i, r)
   const int row0 = r0 + NB * (lane & 15);
   auto col = [&](int i, int r) { return c0 + NB * Mma<E>::col(lane, r) + i; };
@@ -382,9 +398,8 @@ __device__ __forceinline__ void update_products(const ExecMat& M, const Task& w,
         if (mode == 0) v[j] = !diag || row0 + j >= col(i, r) ? cin[i][r][j] - x : cin[i][r][j];
         else v[j] = accum && active ? cin[i][r][j] + x : x;
       }
-      GLOBAL double* o = out + row0 + col(i, r) * T;
-      if constexpr (NB == 2) st_dev((GLOBAL v2d*)o, v2d{v[0], v[NB - 1]});
-      else st_dev(o, v[0]);
+      if constexpr (NB == 2) dev.store(row0 + col(i, r) * T, v2d{v[0], v[NB - 1]});
+      else dev.store(row0 + col(i, r) * T, v[0]);
     }
 }
 
@@ -1156,69 +1171,116 @@ __device__ __forceinline__ void task_fsum(const ExecMat& M, const Task& w, int n
 }
 
 // ------------------------------------------------------- selected inversion
-// Tile products of the form C = op(X) op(Y)^T, op = identity or transpose,
-// on tiles staged in LDS with leading dimension LP = T + 2: reading a
-// column-major tile directly or transposed is then free of bank conflicts
-// within each group of 16 lanes, and the 16-byte staging stores stay aligned.
-// Each wave owns one (T/2) x (T/2) quarter: acc[i][j] covers its rows
-// 16 j + (lane & 15) and columns 16 i + (lane >> 4) + 4 r.
-
+// Tile products C = op(X) Y, op = identity or transpose, on whole tiles in
+// LDS, each wave a (T/2) x (T/2) quarter: acc[i][j] covers its rows
+// NB li + j and columns NB m + i (NB = T/32, li = lane & 15,
+// m = (lane >> 4) + 4 r), as in update_products.  Y, and X when transposed,
+// are read down their columns: lane group lk = lane >> 4 takes
+// k = 8 s + 2 lk and the next one for two MFMA steps, a 16-byte read (the
+// order of k within eight is free as long as X and Y agree); X as stored is
+// read along its rows, NB of one column at a time.  Tile element (row, col)
+// is in 16-byte unit row/2 of its column, and the units of a column are
+// permuted by an XOR with a function of the column: every one of these reads
+// and the 16-byte staging and result stores then cover all LDS banks.
 template <int T>
-struct PadStage {
-  typedef double d2 __attribute__((ext_vector_type(2)));
-  static constexpr int LP = T + 2;
-  static constexpr int NV = T * T / NT / 2;
-  d2 r[NV];
-  __device__ __forceinline__ void load(const double* __restrict__ g) {
-    const GLOBAL d2* v = (const GLOBAL d2*)g;
-#pragma unroll
-    for (int q = 0; q < NV; q++) r[q] = v[thread_id() + q * NT];
+struct Swz {
+  static constexpr int NB = T / 32;
+  // unit permutation of a column: the columns NB li + q of a read down the
+  // columns get 16 different ones; T = 32: bits 1 and 3 exchanged, so that
+  // 8-byte reads along rows by two lane groups fall into different halves
+  __device__ __forceinline__ static int g(int col) {
+    return T == 64 ? (col >> 1) & 15 : ((col & 2) << 2) | ((col & 8) >> 2) | (col & 5);
   }
-  __device__ __forceinline__ void store(double* l) const {
-#pragma unroll
-    for (int q = 0; q < NV; q++) {
-      const int e = 2 * (thread_id() + q * NT);
-      *reinterpret_cast<d2*>(l + (e % T) + (e / T) * LP) = r[q];
-    }
+  // byte offset of element (row, col), of its unit if row is even
+  __device__ __forceinline__ static int at(int row, int col) {
+    return col * T * 8 + (((row >> 1) ^ g(col)) << 4) + (row & 1) * 8;
   }
 };
 
-// acc += op(X) op(Y)^T: Xe(row, kk) = TX ? X[kk + row LP] : X[row + kk LP],
-// the same for Y (rows of C from X, columns from Y)
-template <int T, bool TX, bool TY>
-__device__ __forceinline__ void mma_lp(v4d (&acc)[T / 32][T / 32], const double* X, const double* Y, int r0, int c0,
-                                       int lane) {
-  constexpr int NB = T / 32, LP = T + 2;
-  const int li = lane & 15, lk = lane >> 4;
-  auto ya = [&](int q, int kk) { const int yi = c0 + 16 * q + li; return TY ? Y[kk + yi * LP] : Y[yi + kk * LP]; };
-  auto xb = [&](int q, int kk) { const int xi = r0 + 16 * q + li; return TX ? X[kk + xi * LP] : X[xi + kk * LP]; };
-  double a[NB], b[NB];
+
+template <int T>
+struct TileRegs {
+  static constexpr int NV = T * T / NT / 2;
+  v2d r[NV];
+  __device__ __forceinline__ void load(const double* __restrict__ g) {
+    const GLOBAL v2d* v = (const GLOBAL v2d*)g;
 #pragma unroll
-  for (int q = 0; q < NB; q++) {
-    a[q] = ya(q, lk);
-    b[q] = xb(q, lk);
+    for (int q = 0; q < NV; q++) r[q] = v[thread_id() + q * NT];
   }
+  __device__ __forceinline__ v2d* at(double* l, int q) const {
+    const int e = 2 * (thread_id() + q * NT);
+    return reinterpret_cast<v2d*>((char*)l + Swz<T>::at(e % T, e / T));
+  }
+  __device__ __forceinline__ void store(double* l) const {
 #pragma unroll
-  for (int k = 0; k < T; k += 4) {
-    double an[NB], bn[NB];
-    if (k + 4 < T) {
+    for (int q = 0; q < NV; q++) *at(l, q) = r[q];
+  }
+};
+
+// acc += op(X) Y, op = transpose if TX.  The operands of the next two MFMA
+// steps are read while these run.  With 8-byte reads on padded tiles the
+// reads held up the matrix cores (81 cycles per MFMA against 69).
+template <int T, bool TX>
+__device__ __forceinline__ void mma_tiles(v4d (&acc)[T / 32][T / 32], const double* X, const double* Y, int r0, int c0,
+                                          int lane) {
+  constexpr int NB = T / 32, CB = T * 8;   // CB: bytes of a column
+  const int li = lane & 15, lk = lane >> 4;
+  const int yo = Swz<T>::at(2 * lk, c0 + NB * li);
+  const int xo = TX ? Swz<T>::at(2 * lk, r0 + NB * li) : Swz<T>::at(r0 + NB * li, 2 * lk);
+  // down the columns: eight rows further is four units further, an XOR
+  auto down = [&](const double* Z, int o, int q, int k) {
+    return *reinterpret_cast<const v2d*>((const char*)Z + ((o ^ (k << 3)) + q * CB));
+  };
+  // two steps' operands: z[step][block]
+  auto read = [&](double (&a)[2][NB], double (&b)[2][NB], int k) {
 #pragma unroll
-      for (int q = 0; q < NB; q++) {
-        an[q] = ya(q, k + 4 + lk);
-        bn[q] = xb(q, k + 4 + lk);
+    for (int q = 0; q < NB; q++) {
+      const v2d y = down(Y, yo, q, k);
+      a[0][q] = y[0];
+      a[1][q] = y[1];
+      if constexpr (TX) {
+        const v2d x = down(X, xo, q, k);
+        b[0][q] = x[0];
+        b[1][q] = x[1];
       }
     }
+    if constexpr (!TX) {
+      if constexpr (NB == 2) {   // columns k + 2 lk and the next: the same unit permutation
+        const char* x = (const char*)X + ((xo ^ (8 * k & 255)) + k * CB);
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+          const v2d v = *reinterpret_cast<const v2d*>(x + h * CB);
+          b[h][0] = v[0];
+          b[h][NB - 1] = v[1];
+        }
+      } else {
+        const int o = (xo ^ ((k & 8) << 2)) + k * CB;
+        b[0][0] = *reinterpret_cast<const double*>((const char*)X + o);
+        b[1][0] = *reinterpret_cast<const double*>((const char*)X + ((o ^ 16) + CB));
+      }
+    }
+  };
+  double a[2][NB], b[2][NB];
+  read(a, b, 0);
+#pragma unroll
+  for (int k = 0; k < T; k += 8) {
+    double an[2][NB], bn[2][NB];
+    if (k + 8 < T) read(an, bn, k + 8);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < NB; i++)
+    for (int h = 0; h < 2; h++)
 #pragma unroll
-      for (int j = 0; j < NB; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    if (k + 4 < T) {
+      for (int i = 0; i < NB; i++)
 #pragma unroll
-      for (int q = 0; q < NB; q++) {
-        a[q] = an[q];
-        b[q] = bn[q];
-      }
+        for (int j = 0; j < NB; j++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h][i], b[h][j], acc[i][j], 0, 0, 0);
+    if (k + 8 < T) {
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int q = 0; q < NB; q++) {
+          a[h][q] = an[h][q];
+          b[h][q] = bn[h][q];
+        }
     }
   }
 }
@@ -1231,111 +1293,221 @@ __device__ __forceinline__ void zero_acc(v4d (&acc)[T / 32][T / 32]) {
     for (int j = 0; j < T / 32; j++) acc[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
 }
 
-// acc += sum over pairs of Sig~ L: the pair words (Sigma tile code, L tile)
-// are in pv (at most 32 pairs); LX, LY: padded LDS tiles.  Two register
-// stages alternate, so the global loads of a pair are issued two products
-// before it is used.
+// C = Sig~ L on LDS tiles: Sig~ as stored or transposed
 template <int T>
-__device__ __forceinline__ void sig_pair_load(PadStage<T>& sx, PadStage<T>& sy, const ExecMat& M, int pv, int p) {
-  constexpr int TT = T * T;
-  sx.load(M.sigma + (int64_t)(word(pv, 2 * p) & ~SIG_TRANS) * TT);
-  sy.load(M.tiles + (int64_t)word(pv, 2 * p + 1) * TT);
+__device__ __forceinline__ void sig_mma(v4d (&acc)[T / 32][T / 32], int code, const double* LX, const double* LY,
+                                        int r0, int c0, int lane) {
+  if (code & SIG_TRANS) mma_tiles<T, true>(acc, LX, LY, r0, c0, lane);
+  else mma_tiles<T, false>(acc, LX, LY, r0, c0, lane);
 }
 
+// this lane's elements of a quarter: NB rows row0 .., columns col(i, r)
 template <int T>
-__device__ __forceinline__ void sig_pair_mma(v4d (&acc)[T / 32][T / 32], int code, const double* LX, const double* LY,
-                                             int r0, int c0, int lane) {
-  // C = Sig~ L: op(X) = Sig or Sig^T, op(Y)^T = L
-  if (code & SIG_TRANS) mma_lp<T, true, true>(acc, LX, LY, r0, c0, lane);
-  else mma_lp<T, false, true>(acc, LX, LY, r0, c0, lane);
-}
+struct Quarter {
+  static constexpr int NB = T / 32;
+  typedef double vec __attribute__((ext_vector_type(NB)));
+  int row0, c0m;
+  __device__ __forceinline__ Quarter(int r0, int c0, int lane) : row0(r0 + NB * (lane & 15)), c0m(c0 + NB * (lane >> 4)) {}
+  __device__ __forceinline__ int col(int i, int r) const { return c0m + 4 * NB * r + i; }
+};
 
-template <int T>
-__device__ __forceinline__ void sig_products(v4d (&acc)[T / 32][T / 32], const ExecMat& M, int pv, int np,
-                                             double* LX, double* LY, int r0, int c0, int lane) {
-  if (np <= 0) return;
-  PadStage<T> ax, ay, bx, by;
-  sig_pair_load<T>(ax, ay, M, pv, 0);
-  if (np > 1) sig_pair_load<T>(bx, by, M, pv, 1);
-  for (int p = 0; p < np; p += 2) {
-    __syncthreads();
-    ax.store(LX);
-    ay.store(LY);
-    __syncthreads();
-    if (p + 2 < np) sig_pair_load<T>(ax, ay, M, pv, p + 2);
-    sig_pair_mma<T>(acc, word(pv, 2 * p), LX, LY, r0, c0, lane);
-    if (p + 1 < np) {
-      __syncthreads();
-      bx.store(LX);
-      by.store(LY);
-      __syncthreads();
-      if (p + 3 < np) sig_pair_load<T>(bx, by, M, pv, p + 3);
-      sig_pair_mma<T>(acc, word(pv, 2 * p + 2), LX, LY, r0, c0, lane);
-    }
-  }
-}
-
-// out (global, column-major T x T) <- s * acc, element by element
+// out (global, column-major T x T) <- s * acc
 template <int T>
 __device__ __forceinline__ void put_acc_g(const v4d (&acc)[T / 32][T / 32], double* out, double sc, int r0, int c0,
                                           int lane) {
-  GLOBAL double* o = gp(out);
+  constexpr int NB = T / 32;
+  const Quarter<T> e(r0, c0, lane);
+  const DevTile<T> dev(out);
 #pragma unroll
-  for (int i = 0; i < T / 32; i++)
+  for (int i = 0; i < NB; i++)
 #pragma unroll
-    for (int j = 0; j < T / 32; j++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-        st_dev(o + row + col * T, sc * acc[i][j][r]);
-      }
+    for (int r = 0; r < 4; r++) {
+      const int q = e.row0 + e.col(i, r) * T;
+      if constexpr (NB == 2) dev.store(q, v2d{sc * acc[i][0][r], sc * acc[i][NB - 1][r]});
+      else dev.store(q, sc * acc[i][0][r]);
+    }
 }
 
-// out (LDS, leading dimension T + 2) <- s * acc
+// out (LDS tile) <- s * acc
 template <int T>
 __device__ __forceinline__ void put_acc_l(const v4d (&acc)[T / 32][T / 32], double* out, double sc, int r0, int c0,
                                           int lane) {
+  constexpr int NB = T / 32;
+  const Quarter<T> e(r0, c0, lane);
 #pragma unroll
-  for (int i = 0; i < T / 32; i++)
+  for (int i = 0; i < NB; i++)
 #pragma unroll
-    for (int j = 0; j < T / 32; j++)
+    for (int r = 0; r < 4; r++) {
+      typename Quarter<T>::vec v;
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-        out[row + col * (T + 2)] = sc * acc[i][j][r];
-      }
+      for (int j = 0; j < NB; j++) v[j] = sc * acc[i][j][r];
+      *reinterpret_cast<typename Quarter<T>::vec*>((char*)out + Swz<T>::at(e.row0, e.col(i, r))) = v;
+    }
 }
 
 // acc += tile g (column-major T x T, global), element by element
 template <int T>
 __device__ __forceinline__ void add_tile(v4d (&acc)[T / 32][T / 32], const double* __restrict__ g, int r0, int c0,
                                          int lane) {
-  const GLOBAL double* s = gp(g);
+  constexpr int NB = T / 32;
+  const Quarter<T> e(r0, c0, lane);
+  const GLOBAL double* s = gp(g) + e.row0;
 #pragma unroll
-  for (int i = 0; i < T / 32; i++)
+  for (int i = 0; i < NB; i++)
 #pragma unroll
-    for (int j = 0; j < T / 32; j++)
+    for (int r = 0; r < 4; r++) {
+      const typename Quarter<T>::vec v = *(const GLOBAL typename Quarter<T>::vec*)(s + e.col(i, r) * T);
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-        acc[i][j][r] += s[row + col * T];
+      for (int j = 0; j < NB; j++) acc[i][j][r] += v[j];
+    }
+}
+
+// acc += sum over the np pairs of pv of Sig~ L (pair words: Sigma tile code,
+// L tile), streamed through the operand ring of the update products (Ring)
+// in stages of KS values of k.  Sig as stored: KS whole columns, in memory
+// order.  L, and Sig transposed: KS rows of every column; a column's
+// KS / 2 units of 16 bytes form one row of the slot, the columns ordered so
+// that a lane's blocks are 16 slot rows apart and the units of a slot row
+// permuted by an XOR, so that the 16-byte reads cover all LDS banks.  The
+// transfers do this order by each lane's own global address.  A product
+// takes 2.84 us on an otherwise idle CU (tiles staged whole through registers
+// 3.13; the MFMAs alone 1.9) and 5.4 us with the chip full (6.1), when the
+// operands' traffic binds; selected inversion of the n = 200,000
+// variable-band matrix 13.5 -> 11.8 ms.
+template <int T>
+__device__ __forceinline__ void sig_products(v4d (&acc)[T / 32][T / 32], const ExecMat& M, int pv, int np, double* ring,
+                                             int r0, int c0) {
+  typedef Ring<T, double> R;
+  constexpr int NB = T / 32, NI = R::NI, NST = R::NST, KS = R::KS;
+  constexpr int CB = T * 8, SB = KS * 8;      // bytes of a tile column, of a slot row
+  const int tid = thread_id(), lane = tid & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring + 1024 * wave;
+  // unit permutation of a slot row
+  auto perm = [](int sr) { return NB == 2 ? (sr >> 1) & 7 : sr & 15; };
+  const uint32_t voff = 1024 * wave + 16 * lane;
+  uint32_t vrow;   // by rows: transfer i of a stage adds i (4096 / SB) columns
+  {
+    const int sr = (int)voff / SB, unit = ((int)voff % SB / 16) ^ perm(sr);
+    const int c = NB == 2 ? 2 * (sr & 15) + (sr >> 4) : sr;
+    vrow = c * CB + 16 * unit;
+  }
+  const int total = np * R::SPP;
+  const double *const sigma = M.sigma, *const tiles = M.tiles;
+  const char *xb, *yb;
+  uint32_t dst;
+  bool xtr;
+  auto stage = [&](int s, int slot) {
+    const int p = s / R::SPP, h = s % R::SPP;
+    const int code = word(pv, 2 * p);
+    xtr = (code & SIG_TRANS) != 0;
+    xb = (const char*)(sigma + (int64_t)(code & ~SIG_TRANS) * T * T) + h * (xtr ? SB : R::HB);
+    yb = (const char*)(tiles + (int64_t)word(pv, 2 * p + 1) * T * T) + h * SB;
+    dst = lds0 + (uint32_t)slot * 2 * R::HB;
+  };
+  auto transfer = [&](int i) {
+    const int c = i % (NI / 2);
+    if (i < NI / 2) lds_transfer(dst + 4096 * c, xtr ? vrow + 4096 / SB * CB * c : voff + 4096 * c, xb);
+    else lds_transfer(dst + R::HB + 4096 * c, vrow + 4096 / SB * CB * c, yb);
+  };
+#pragma unroll
+  for (int s = 0; s < NST - 1; s++)
+    if (s < total) {
+      stage(s, s);
+#pragma unroll
+      for (int i = 0; i < NI; i++) transfer(i);
+    }
+  ring_barrier<NI>((total < NST - 1 ? total : NST - 1) * NI - NI);
+  // byte offsets within a slot: X as stored, X by rows, Y
+  const int xd = (r0 + NB * li) * 8 + 2 * lk * CB;
+  const int xt = (r0 + li) * SB + ((lk ^ perm(li)) << 4);
+  const int yo = (c0 + li) * SB + ((lk ^ perm(li)) << 4) + R::HB;
+  constexpr int SLOT = 2 * R::HB;
+  auto trans = [&](int s) { return (word(pv, 2 * (s / R::SPP)) & SIG_TRANS) != 0; };
+  // operands of two MFMA steps, k .. k + 7 of a slot
+  auto read = [&](double (&a)[2][NB], double (&b)[2][NB], const char* slot, int k, bool tr) {
+#pragma unroll
+    for (int q = 0; q < NB; q++) {
+      const v2d y = *reinterpret_cast<const v2d*>(slot + ((yo ^ (k << 3)) + 16 * SB * q));
+      a[0][q] = y[0];
+      a[1][q] = y[1];
+    }
+    if constexpr (NB == 2) {
+      const char* x = slot + (tr ? xt ^ (k << 3) : xd + k * CB);
+      const v2d u = *reinterpret_cast<const v2d*>(x);
+      const v2d v = *reinterpret_cast<const v2d*>(x + (tr ? 16 * SB : CB));
+      b[0][0] = u[0];
+      b[0][NB - 1] = tr ? v[0] : u[1];
+      b[1][0] = tr ? u[1] : v[0];
+      b[1][NB - 1] = v[1];
+    } else if (tr) {
+      const v2d u = *reinterpret_cast<const v2d*>(slot + (xt ^ (k << 3)));
+      b[0][0] = u[0];
+      b[1][0] = u[1];
+    } else {
+      b[0][0] = *reinterpret_cast<const double*>(slot + (xd + k * CB));
+      b[1][0] = *reinterpret_cast<const double*>(slot + (xd + (k + 1) * CB));
+    }
+  };
+  int slot = 0, wslot = NST - 1;
+  bool tr = trans(0);
+  double a[2][NB], b[2][NB];
+  read(a, b, (const char*)ring, 0, tr);
+#pragma unroll 1
+  for (int s = 0; s < total; s++) {
+    const char* cur = (const char*)ring + slot * SLOT;
+    slot = slot + 1 == NST ? 0 : slot + 1;
+    const char* nxt = (const char*)ring + slot * SLOT;
+    const bool more = s + NST - 1 < total;
+    const bool trn = s + 1 < total ? trans(s + 1) : tr;
+#pragma unroll
+    for (int k = 0; k < KS; k += 8) {
+      double an[2][NB], bn[2][NB];
+      if (k + 8 < KS) read(an, bn, cur, k + 8, tr);
+      else read(an, bn, nxt, 0, trn);
+      if (k >= 8 && more) {
+#pragma unroll
+        for (int i = (k / 8 - 1) * NI / (KS / 8 - 1); i < (k / 8) * NI / (KS / 8 - 1); i++) transfer(i);
       }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int i = 0; i < NB; i++)
+#pragma unroll
+          for (int j = 0; j < NB; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h][i], b[h][j], acc[i][j], 0, 0, 0);
+      if (k == 0) {
+        // the next stage has arrived, the previous one's slot is free
+        const int last = s + NST - 2 < total ? s + NST - 2 : total - 1;
+        if (s + 1 < total) ring_barrier<NI>((last - (s + 1)) * NI);
+        if (more) stage(s + NST - 1, wslot);
+        wslot = wslot + 1 == NST ? 0 : wslot + 1;
+      }
+#pragma unroll
+      for (int h = 0; h < 2; h++)
+#pragma unroll
+        for (int q = 0; q < NB; q++) {
+          a[h][q] = an[h][q];
+          b[h][q] = bn[h][q];
+        }
+    }
+    tr = trn;
+  }
 }
 
 // SWE: W_t (+)= sum over pairs of Sig~ L, kept in the Sigma tile of t until
 // its SW task finishes it
 template <int T>
-__device__ __forceinline__ void task_swe(const ExecMat& M, const Task& w, double* LX, double* LY) {
+__device__ __forceinline__ void task_swe(const ExecMat& M, const Task& w, double* ring) {
   constexpr int TT = T * T, W = T / 2, NB = T / 32;
   const int lane = thread_id() & 63, wave = thread_id() >> 6;
   const int r0 = (wave >> 1) * W, c0 = (wave & 1) * W;
   double* out = M.sigma + (int64_t)w[1] * TT;
-  const int np = w[3];
-  const int pv = w.pv;
   v4d acc[NB][NB];
   zero_acc<T>(acc);
   if (w[0] & TF_ACC) add_tile<T>(acc, out, r0, c0, lane);
-  sig_products<T>(acc, M, pv, np, LX, LY, r0, c0, lane);
+  sig_products<T>(acc, M, w.pv, w[3], ring, r0, c0);
   put_acc_g<T>(acc, out, 1.0, r0, c0, lane);
 }
 
@@ -1346,7 +1518,7 @@ template <int T>
 __device__ __forceinline__ void selinv_prefetch(const ExecMat& M, const Task& w, double* LX, double* LY) {
   constexpr int TT = T * T;
   const int type = w[0] & 0xff;
-  PadStage<T> st;
+  TileRegs<T> st;
   if (type == TK_SW) {
     st.load(M.tiles + (int64_t)word(w.pv, 1) * TT);
     st.store(LY);
@@ -1373,7 +1545,7 @@ __device__ __forceinline__ void task_sw(const ExecMat& M, const Task& w, double*
   const int64_t t = w[1];
   const int64_t k = w[2];
   double* sig = M.sigma + t * TT;
-  PadStage<T> sx, sy, st;
+  TileRegs<T> sx, sy, st;
   sx.load(M.sigma + (int64_t)(word(pv, 0) & ~SIG_TRANS) * TT);
   if (nprod > 1) {
     sy.load(M.tiles + (int64_t)word(pv, 3) * TT);
@@ -1387,33 +1559,33 @@ __device__ __forceinline__ void task_sw(const ExecMat& M, const Task& w, double*
   for (int q = 0; q < nsum; q++) add_tile<T>(acc, M.qpart + (int64_t)word(pv, sw0 + q) * TT, r0, c0, lane);
   sx.store(LX);
   __syncthreads();
-  // W += Sig~ L_y  (op(X) = Sig or Sig^T, op(Y)^T = L_y)
-  sig_pair_mma<T>(acc, word(pv, 0), LX, LY, r0, c0, lane);
+  // W += Sig~ L_y
+  sig_mma<T>(acc, word(pv, 0), LX, LY, r0, c0, lane);
   if (nprod > 1) {
     __syncthreads();
     st.store(LX);
     sy.store(LY);
     __syncthreads();
     st.load(M.linv + k * TT);
-    sig_pair_mma<T>(acc, word(pv, 2), LX, LY, r0, c0, lane);
+    sig_mma<T>(acc, word(pv, 2), LX, LY, r0, c0, lane);
   }
-  // Sig_t = -W Linv_k  (op(X) = W, op(Y)^T = Linv_k)
+  // Sig_t = -W Linv_k
   __syncthreads();
   put_acc_l<T>(acc, LX, 1.0, r0, c0, lane);
   st.store(LY);
   __syncthreads();
   st.load(M.tiles + t * TT);
   zero_acc<T>(acc);
-  mma_lp<T, false, true>(acc, LX, LY, r0, c0, lane);
+  mma_tiles<T, false>(acc, LX, LY, r0, c0, lane);
   put_acc_g<T>(acc, sig, -1.0, r0, c0, lane);
   __syncthreads();
   put_acc_l<T>(acc, LX, -1.0, r0, c0, lane);   // LX = Sig_t
   st.store(LY);                                // LY = L_t
   __syncthreads();
   if (npush > 0) st.load(M.tiles + (int64_t)word(pv, pw0) * TT);
-  // D_t = L_t^T Sig_t  (op(X) = L_t^T, op(Y)^T = Sig_t)
+  // D_t = L_t^T Sig_t
   zero_acc<T>(acc);
-  mma_lp<T, true, true>(acc, LY, LX, r0, c0, lane);
+  mma_tiles<T, true>(acc, LY, LX, r0, c0, lane);
   put_acc_g<T>(acc, M.dpart + t * TT, 1.0, r0, c0, lane);
   for (int q = 0; q < npush; q++) {
     const int64_t u = word(pv, pw0 + q);
@@ -1421,9 +1593,9 @@ __device__ __forceinline__ void task_sw(const ExecMat& M, const Task& w, double*
     st.store(LY);                              // LY = L_u
     __syncthreads();
     if (q + 1 < npush) st.load(M.tiles + (int64_t)word(pv, pw0 + q + 1) * TT);
-    // Q_u = Sig_t^T L_u  (op(X) = Sig_t^T, op(Y)^T = L_u)
+    // Q_u = Sig_t^T L_u
     zero_acc<T>(acc);
-    mma_lp<T, true, true>(acc, LX, LY, r0, c0, lane);
+    mma_tiles<T, true>(acc, LX, LY, r0, c0, lane);
     put_acc_g<T>(acc, M.qpart + u * TT, 1.0, r0, c0, lane);
   }
 }
@@ -1433,42 +1605,47 @@ __device__ __forceinline__ void task_sw(const ExecMat& M, const Task& w, double*
 // stored tile is symmetric.  Linv_k was staged in LX by selinv_prefetch.
 template <int T>
 __device__ __forceinline__ void task_sdiag(const ExecMat& M, const Task& w, double* LX, double* LY) {
-  constexpr int TT = T * T, W = T / 2, NB = T / 32, LP = T + 2;
+  constexpr int TT = T * T, W = T / 2, NB = T / 32;
   typedef double d2 __attribute__((ext_vector_type(2)));
   const int lane = thread_id() & 63, wave = thread_id() >> 6;
   const int r0 = (wave >> 1) * W, c0 = (wave & 1) * W;
   const int nd = w[4];
   const int pv = w.pv;
-  PadStage<T> z;
+  TileRegs<T> z;
 #pragma unroll
-  for (int v = 0; v < PadStage<T>::NV; v++) {
-    const int e = 2 * (thread_id() + v * NT);
-    z.r[v] = *reinterpret_cast<const d2*>(LX + (e % T) + (e / T) * LP);
-  }
+  for (int v = 0; v < TileRegs<T>::NV; v++) z.r[v] = *z.at(LX, v);
   for (int q = 0; q < nd; q++) {
     const GLOBAL d2* dp = (const GLOBAL d2*)(M.dpart + (int64_t)word(pv, q) * TT);
 #pragma unroll
-    for (int v = 0; v < PadStage<T>::NV; v++) z.r[v] -= dp[thread_id() + v * NT];
+    for (int v = 0; v < TileRegs<T>::NV; v++) z.r[v] -= dp[thread_id() + v * NT];
   }
   z.store(LY);
   __syncthreads();
   v4d acc[NB][NB];
   zero_acc<T>(acc);
-  // op(X) = Linv_k^T, op(Y)^T = Z
-  mma_lp<T, true, true>(acc, LX, LY, r0, c0, lane);
-  GLOBAL double* out = gp(M.sigma + (int64_t)w[1] * TT);
+  // Linv_k^T Z
+  mma_tiles<T, true>(acc, LX, LY, r0, c0, lane);
+  const DevTile<T> out(M.sigma + (int64_t)w[1] * TT);
+  const Quarter<T> e(r0, c0, lane);
 #pragma unroll
-  for (int i = 0; i < NB; i++)
-#pragma unroll
-    for (int j = 0; j < NB; j++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int row = r0 + 16 * j + (lane & 15), col = c0 + 16 * i + (lane >> 4) + 4 * r;
-        if (row >= col) {
-          st_dev(out + row + col * T, acc[i][j][r]);
-          st_dev(out + col + row * T, acc[i][j][r]);
-        }
+  for (int r = 0; r < 4; r++) {
+    const int row = e.row0, col = e.col(0, r);   // NB x NB elements from here
+    if constexpr (NB == 2) {
+      // (above the diagonal: the mirrored element of a diagonal 2 x 2 block)
+      const double up = row == col ? acc[0][NB - 1][r] : acc[NB - 1][0][r];
+      if (row >= col) {
+        out.store(row + col * T, v2d{acc[0][0][r], acc[0][NB - 1][r]});
+        out.store(row + (col + 1) * T, v2d{up, acc[NB - 1][NB - 1][r]});
       }
+      if (row > col) {
+        out.store(col + row * T, v2d{acc[0][0][r], acc[NB - 1][0][r]});
+        out.store(col + (row + 1) * T, v2d{acc[0][NB - 1][r], acc[NB - 1][NB - 1][r]});
+      }
+    } else if (row >= col) {
+      out.store(row + col * T, acc[0][0][r]);
+      out.store(col + row * T, acc[0][0][r]);
+    }
+  }
 }
 
 // TSUM: slot w1 = sum of the listed slots of dpart (c = 0) or qpart (c = 1),
@@ -1477,10 +1654,10 @@ template <int T>
 __device__ __forceinline__ void task_tsum(const ExecMat& M, const Task& w) {
   constexpr int TT = T * T;
   typedef double d2 __attribute__((ext_vector_type(2)));
-  const double* base = w[4] == 1 ? M.qpart : M.dpart;
+  double* base = w[4] == 1 ? M.qpart : M.dpart;
   const int32_t* lst = M.pairs + w[2];
   const int n = w[3];
-  GLOBAL d2* out = (GLOBAL d2*)(base + (int64_t)w[1] * TT);
+  const DevTile<T> out(base + (int64_t)w[1] * TT);
   constexpr int NV = TT / 2 / NT;
   d2 s0[NV], s1[NV], s2[NV], s3[NV];
 #pragma unroll
@@ -1513,9 +1690,7 @@ __device__ __forceinline__ void task_tsum(const ExecMat& M, const Task& w) {
 #pragma unroll
   for (int v = 0; v < NV; v++) {
     const d2 t = (s0[v] + s1[v]) + (s2[v] + s3[v]);
-    GLOBAL double* o = (GLOBAL double*)(out + thread_id() + v * NT);
-    st_dev(o, t.x);
-    st_dev(o + 1, t.y);
+    out.store(2 * (thread_id() + v * NT), t);
   }
 }
 
@@ -1565,10 +1740,11 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
   constexpr bool SOLVE = KIND == EXEC_SOLVE, SELINV = KIND == EXEC_SELINV, BOTH = KIND == EXEC_FACTOR_SOLVE;
   // LDS: factorization tasks use S (a tile; POTRF: leading dimension T + 17)
   // and Xi (T x T) or, updates, the whole as a ring; solve tasks only a
-  // T x 16 block of Xi; selected-inversion tasks two padded tiles.
-  constexpr int NS = SOLVE ? 2 : SELINV ? T * (T + 2) : T * (T + 17);
-  constexpr int NX = SOLVE ? T * 16 : SELINV ? T * (T + 2) : T * T;
-  constexpr int NR = SOLVE || SELINV ? 0 : Ring<T, double>::NST * 2 * Ring<T, double>::HB / 8;
+  // T x 16 block of Xi; selected-inversion tasks two tiles or
+  // the ring.
+  constexpr int NS = SOLVE ? 2 : SELINV ? T * T : T * (T + 17);
+  constexpr int NX = SOLVE ? T * 16 : T * T;
+  constexpr int NR = SOLVE ? 0 : Ring<T, double>::NST * 2 * Ring<T, double>::HB / 8;
   __shared__ __attribute__((aligned(1024))) double S[NS + NX > NR ? NS + NX : NR];
   double* const Xi = S + NS;
   __shared__ int32_t s_ticket;
@@ -1628,7 +1804,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
     if (chain) __builtin_amdgcn_s_setprio(3);
     if constexpr (SELINV) {
       if (!ok) {
-      } else if (type == TK_SWE) task_swe<T>(M, w, S, Xi);
+      } else if (type == TK_SWE) task_swe<T>(M, w, S);
       else if (type == TK_SW) task_sw<T>(M, w, S, Xi);
       else if (type == TK_SDIAG) task_sdiag<T>(M, w, S, Xi);
       else task_tsum<T>(M, w);
