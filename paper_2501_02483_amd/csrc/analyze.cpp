@@ -94,6 +94,40 @@ std::vector<int32_t> list_order(int32_t nt, const float* cost, const int32_t* su
   return order;
 }
 
+// Chain pairs: a POTRF that waits late for a TRSM is run by that TRSM's
+// workgroup (TF_CHAIN on both) if its other predecessors all have earlier
+// tickets; those that can be moved ahead of the TRSM are.  A workgroup then
+// still waits only for tasks of earlier tickets, also inside a pair.
+void chain_pairs(TaskBuilder& tb, std::vector<int32_t>& order) {
+  const int32_t nt = (int32_t)order.size();
+  auto type = [&](int32_t t) { return tb.words[(size_t)t * TASK_WORDS] & 0xff; };
+  std::vector<int32_t> potrf(nt, -1), out, miss;
+  for (int32_t y = 0; y < nt; y++)
+    if (type(y) == TK_POTRF && tb.late[y] >= 0 && type(tb.late[y]) == TK_TRSM) potrf[tb.late[y]] = y;
+  std::vector<char> done(nt, 0);
+  auto emit = [&](int32_t t) { out.push_back(t); done[t] = 1; };
+  for (int32_t t : order) {
+    if (done[t]) continue;
+    const int32_t y = potrf[t];
+    if (y >= 0) {
+      miss.clear();
+      bool ok = true;
+      for (int32_t p : tb.preds[y]) {
+        if (p == t || done[p]) continue;
+        for (int32_t q : tb.preds[p]) ok = ok && done[q];
+        miss.push_back(p);
+      }
+      if (ok) {
+        for (int32_t p : miss) emit(p);
+        tb.words[(size_t)t * TASK_WORDS] |= TF_CHAIN;
+        tb.words[(size_t)y * TASK_WORDS] |= TF_CHAIN;
+      }
+    }
+    emit(t);
+  }
+  order.swap(out);
+}
+
 // workgroups of the list schedule: a full-GPU executor launch has two per CU
 // on 256 CUs; -1 (option) = unbounded earliest-start order
 int sched_workers(const stiles_opts& o) { return o.sched_workers == 0 ? 512 : o.sched_workers < 0 ? 0 : o.sched_workers; }
@@ -130,14 +164,14 @@ void schedule(TaskBuilder& tb, std::vector<int32_t>& tasks_out, std::vector<int3
     bl[t] = b + tb.cost[t];
   }
   std::vector<int32_t> order(nt);
+  double tot = 0.0;
+  float blmax = 0.f;
+  for (int t = 0; t < nt; t++) { tot += tb.cost[t]; blmax = std::max(blmax, bl[t]); }
   if (workers > 0) {
     // the list schedule pays off where the pivot chain bounds the run (the
     // critical path is at least half the work per workgroup); on DAGs with
     // far more work than chain (measured: n = 500,000, w = 1,000, ratio 4.2)
     // the earliest-start order is faster
-    double tot = 0.0;
-    float blmax = 0.f;
-    for (int t = 0; t < nt; t++) { tot += tb.cost[t]; blmax = std::max(blmax, bl[t]); }
     if (tot / workers > 2.0 * blmax) workers = 0;
   }
   if (workers <= 0) {
@@ -155,6 +189,13 @@ void schedule(TaskBuilder& tb, std::vector<int32_t>& tasks_out, std::vector<int3
     }
     order = list_order(nt, tb.cost.data(), sptr.data(), sflat.data(), npred.data(), bl.data(), workers, hop);
   }
+  // chain pairs where the pivot chain bounds the run: its length is several
+  // times the work per workgroup.  (Measured against no pairs, by work per
+  // workgroup / critical path: up to 0.02, n = 1,000 to 20,000 in natural or
+  // AMD order, 2.5 to 7.5 % faster; 0.88, 1.9 and 4.2, n = 96,000 to 500,000
+  // under adaptable ND, about 1 % slower: a TRSM's other successors hear of
+  // it later, and another workgroup would have staged the POTRF's tile.)
+  if (tot / 512.0 < 0.25 * blmax) chain_pairs(tb, order);
   std::vector<int32_t> newid(nt);
   for (int i = 0; i < nt; i++) newid[order[i]] = i;
   tasks_out.assign((size_t)nt * TASK_WORDS, 0);
@@ -171,6 +212,9 @@ void schedule(TaskBuilder& tb, std::vector<int32_t>& tasks_out, std::vector<int3
     std::vector<std::pair<int32_t, int32_t>> s;
     for (int x : succ[t]) s.push_back({newid[x], tb.late[x] >= 0 && tb.late[x] != t ? SUCC_FDEP : 0});
     std::sort(s.begin(), s.end());
+    // (a chain pair's POTRF is its TRSM's first successor)
+    if ((w[0] & TF_CHAIN) && (w[0] & 0xff) == TK_TRSM)
+      std::stable_partition(s.begin(), s.end(), [&](const std::pair<int32_t, int32_t>& e) { return tb.late[order[e.first]] == t && (tb.words[(size_t)order[e.first] * TASK_WORDS] & 0xff) == TK_POTRF; });
     for (auto& e : s) succ_out.push_back(e.first | e.second);
     w[6] = (int32_t)succ_out.size();
     if (tb.late[t] >= 0) {
@@ -2031,6 +2075,8 @@ void build_merged(const stiles_symbolic& s, MergedPlan& D) {
     std::vector<int32_t> sl;
     for (int32_t x : succ[t]) sl.push_back(newid[x]);
     std::sort(sl.begin(), sl.end());
+    if ((w[0] & TF_CHAIN) && (w[0] & 0xff) == TK_TRSM)   // its POTRF stays the first successor
+      std::swap(sl[0], *std::find(sl.begin(), sl.end(), newid[s.fsucc[w[5]] & ~SUCC_FDEP]));
     for (int32_t x : sl)
       if (x <= i) { fprintf(stderr, "stiles: merged DAG order is not topological\n"); abort(); }
     w[5] = (int32_t)D.succ.size();

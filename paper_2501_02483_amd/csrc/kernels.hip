@@ -30,6 +30,7 @@ constexpr int NT = 256;
 // are global (not flat) instructions: they then count only in vmcnt, and a
 // wait for LDS data (lgkmcnt) never waits for a tile prefetch in flight.
 #define GLOBAL __attribute__((address_space(1)))
+#define INLINE __attribute__((always_inline))   // lambdas
 template <typename E>
 __device__ __forceinline__ GLOBAL E* gp(E* p) { return (GLOBAL E*)p; }
 template <typename E>
@@ -203,6 +204,34 @@ __device__ __forceinline__ bool wait_below(int32_t* cnt, int32_t bound, ExecCtrl
   return ok;
 }
 
+// Waits until *a < ba (the answer 1) or, failing that, *b < bb (2); 0 if the
+// launch is abandoned.
+__device__ __forceinline__ int wait_first(int32_t* a, int32_t ba, int32_t* b, int32_t bb, ExecCtrl* ctrl,
+                                          uint64_t limit) {
+  __shared__ int32_t s_which;
+  if (thread_id() < 64) {
+    int32_t which = 0;
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+      const int32_t va = ld_relaxed(a), vb = ld_relaxed(b);
+      if (__builtin_amdgcn_readfirstlane(va) < ba) which = 1;
+      else if (__builtin_amdgcn_readfirstlane(vb) < bb) which = 2;
+      if (which != 0) break;
+      if (__builtin_amdgcn_readfirstlane(ld_relaxed(&ctrl->abort)) != 0) break;
+      if (wall_clock64() - t0 > limit) {
+        st_relaxed(&ctrl->abort, 1);
+        break;
+      }
+      __builtin_amdgcn_s_sleep(1);
+    }
+    fence_acquire();
+    if (thread_id() == 0) s_which = which;
+  }
+  __syncthreads();
+  const int which = __builtin_amdgcn_readfirstlane(s_which);
+  __syncthreads();
+  return which;
+}
 
 // ---- operand ring of the update products
 // Tile pairs stream through LDS in stages of KS columns of X and of Y (a
@@ -595,6 +624,27 @@ __device__ __forceinline__ void mma_strip(v4d (&acc)[T / 16], const double* X, c
   }
 }
 
+// A diagonal tile into POTRF's buffer (leading dimension T + 17), with the
+// identity blocks below it.
+template <int T>
+__device__ __forceinline__ void stage_diag(const double* C, double* S) {
+  constexpr int LD = T + 17;
+  const int tid = thread_id();
+  TileStage<T, double> st;
+  st.load(C);
+#pragma unroll
+  for (int q = 0; q < T * 16 / NT; q++) {
+    const int e = tid + q * NT;
+    S[T + (e & 15) + (e >> 4) * LD] = (e & 15) == ((e >> 4) & 15) ? 1.0 : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < TileStage<T, double>::NV; q++) {
+    const int e = 2 * (tid + q * NT);
+    S[(e % T) + (e / T) * LD] = st.r[q].x;
+    S[(e % T) + (e / T) * LD + 1] = st.r[q].y;
+  }
+}
+
 // TRSM: L_t = (C_t - [sum X Y^T]) Linv_k^T; FP32 copy in mixed mode.  The
 // optional fused products (at most two) are the updates with the most recent
 // columns.  The task waits for its predecessors itself: with TF_SPLIT, first
@@ -611,9 +661,14 @@ __device__ __forceinline__ void mma_strip(v4d (&acc)[T / 16], const double* X, c
 // products at T = 64).  Measured from the last wait, one workgroup alone:
 // 4.3 -> 3.0 us at T = 64, 2.4 -> 1.6 us at T = 32 against a product of two
 // staged tiles.
+// A TRSM on the pivot chain (TF_CHAIN) carries the POTRF of the next column
+// with it (next: its counter, C2: its tile): X stays in LDS (LY) for that
+// task, whose tile is staged (in LX) before the last wait if its updates end
+// first.
 template <int T>
 __device__ __forceinline__ uint64_t task_trsm(const ExecMat& M, const Task& w, double* LX, double* LY, int32_t* cnt,
-                                              ExecCtrl* ctrl, uint64_t limit, bool& ok) {
+                                              ExecCtrl* ctrl, uint64_t limit, bool& ok, bool chain, int32_t* next,
+                                              const double* C2, bool& staged) {
   constexpr int TT = T * T, NB = T / 16, NC = NB == 4 ? 4 : 1;   // NC: result blocks per wave
   const int lane = thread_id() & 63, li = lane & 15, lk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(thread_id() >> 6);
@@ -652,7 +707,15 @@ __device__ __forceinline__ uint64_t task_trsm(const ExecMat& M, const Task& w, d
   for (int kb = 0; kb < NB; kb++) c[kb] -= acc[kb];
   if (split) {
     // the POTRF of the column: its inverse is the last operand
-    ok = wait_below(cnt, 1, ctrl, limit);
+    if (chain) {
+      const int which = wait_first(next, 2, cnt, 1, ctrl, limit);
+      ok = which != 0;
+      if (which == 1) {
+        stage_diag<T>(C2, LX);
+        staged = true;
+      }
+    }
+    if (ok) ok = wait_below(cnt, 1, ctrl, limit);
     if (!ok) return 0;
     if (M.trace) t_start = wall_clock64();
   }
@@ -683,6 +746,7 @@ __device__ __forceinline__ uint64_t task_trsm(const ExecMat& M, const Task& w, d
       const int o = (16 * (cb0 + i) + 4 * q) * T;
       st_dev(Cg + o, out[i][q]);
       if (S) st_dev(S + o, (float)out[i][q]);
+      if (chain) LY[r0 + li + lk * T + o] = out[i][q];
     }
   return t_start;
 }
@@ -780,46 +844,41 @@ __device__ __forceinline__ void panel_column(double (&D)[16], double (&a)[16], d
 // the TRSM of its fused operand X = L_(k,k-1) (the panel of the previous
 // column, on the pivot chain).  Returns the time its last wait ended.
 // S: tile buffer with leading dimension T + 17, Xi: T x T (the fused operand).
-template <int T>
-__device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, double* S, double* Xi,
-                                                         int32_t* cnt, ExecCtrl* ctrl, uint64_t limit, bool& ok) {
+// Behind its TRSM in one workgroup (chain): X is in Xi already, and the tile
+// in S if `staged`; `lead` notifies the TRSM's successors, once its stores
+// have completed, after the first panel.  Against two tasks this saves the
+// chain a counter round trip, the completion of X's stores and its way back:
+// n = 10,000, w = 64, natural order 2.82 -> 2.64 ms, 1,000 rows 279 -> 258 us.
+template <int T, class Lead>
+__device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, double* S, double* Xi, int32_t* cnt,
+                                               ExecCtrl* ctrl, uint64_t limit, bool& ok, bool chain, bool staged,
+                                               Lead&& lead) {
   constexpr int TT = T * T, NBK = T / 16, LD = T + 17;
   const int tid = thread_id(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, lk = lane >> 4;
   const bool split = (w[0] & TF_SPLIT) != 0;
-  if (ok) ok = wait_below(cnt, split ? MERGED_FDEP : 1, ctrl, limit);
-  if (!ok) return 0;
-  uint64_t t_start = M.trace ? wall_clock64() : 0;
   double* C = M.tiles + (int64_t)w[1] * TT;
   const int k = w[2];
   // the fused update with column k-1, C_kk -= X X^T, is applied block by
   // block: the first block column before the first panel, the rest by waves
   // 1 to 3 during the first two panels
   const bool fused = w[4] > w[3];
-  {
+  if (!staged) {
+    // (the TRSM it follows does not decrement the counter)
+    ok = wait_below(cnt, chain ? 2 : split ? MERGED_FDEP : 1, ctrl, limit);
+    if (!ok) return 0;
+    stage_diag<T>(C, S);
+  }
+  if (split && !chain) {
+    ok = wait_below(cnt, 1, ctrl, limit);
+    if (!ok) return 0;
+  }
+  const uint64_t t_start = M.trace ? wall_clock64() : 0;
+  if (fused && !chain) {
     TileStage<T, double> st;
-    st.load(C);
-#pragma unroll
-    for (int q = 0; q < T * 16 / NT; q++) {
-      const int e = tid + q * NT;
-      S[T + (e & 15) + (e >> 4) * LD] = (e & 15) == ((e >> 4) & 15) ? 1.0 : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < TileStage<T, double>::NV; q++) {
-      const int e = 2 * (tid + q * NT);
-      S[(e % T) + (e / T) * LD] = st.r[q].x;
-      S[(e % T) + (e / T) * LD + 1] = st.r[q].y;
-    }
-    if (split) {
-      ok = wait_below(cnt, 1, ctrl, limit);
-      if (!ok) return 0;
-      if (M.trace) t_start = wall_clock64();
-    }
-    if (fused) {
-      st.load(M.tiles + (int64_t)word(w.pv, 0) * TT);
-      st.store(Xi);
-    }
+    st.load(M.tiles + (int64_t)word(w.pv, 0) * TT);
+    st.store(Xi);
   }
   __syncthreads();
   // sum of the fused update for block (r, c): 16 rows from each of X's row
@@ -862,17 +921,16 @@ __device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, 
   };
   // stores of panel p by the threads t0 + step i: its columns of L, and its
   // rows of L^{-1}, the transpose of the identity part
-  GLOBAL double* Cg = gp(C);
-  GLOBAL double* Lg = gp(M.linv + (int64_t)k * TT);
+  const DevTile<T> Cd(C), Ld(M.linv + (int64_t)k * TT);
   auto store_panel = [&](int p, int t0, int step) {
-#pragma unroll 4
-    for (int e = t0; e < 16 * T; e += step) {
-      const int row = e % T, col = 16 * p + e / T;
-      const double v = S[row + col * LD];
-      st_dev(Cg + row + col * T, row >= col ? v : 0.0);
-      const int xr = 16 * p + (e & 15), xc = e >> 4;
-      const double x = S[((xr ^ xc) < 16 ? T + (xc & 15) : xc) + xr * LD];
-      st_dev(Lg + xr + xc * T, xr >= xc ? x : 0.0);
+#pragma unroll 2
+    for (int e = t0; e < 8 * T; e += step) {
+      const int xr = 16 * p + 2 * (e & 7), xc = e >> 3;
+      const double* x = S + ((xr ^ xc) < 16 ? T + (xc & 15) : xc) + xr * LD;
+      Ld.store(xr + xc * T, v2d{xr >= xc ? x[0] : 0.0, xr + 1 >= xc ? x[LD] : 0.0});
+      const int row = 2 * e % T, col = 16 * p + 2 * e / T;
+      const double* v = S + row + col * LD;
+      Cd.store(row + col * T, v2d{row >= col ? v[0] : 0.0, row + 1 >= col ? v[1] : 0.0});
     }
   };
   const v4d zero = v4d{0.0, 0.0, 0.0, 0.0};
@@ -930,7 +988,9 @@ __device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, 
         }
       for (int b = p < 2 ? 0 : p - 2; b < (p + 1 == NBK ? p : p - 1); b++) store_panel(b, tid - 64, NT - 64);
     }
+    if (p == 0 && chain) __builtin_amdgcn_s_waitcnt(0);   // X's stores
     __syncthreads();
+    if (p == 0 && chain) lead();
     if (p + 1 < NBK) {
       // the next panel's block column: rows p+1 .. of L, then 0 .. p of the
       // identity part, one block per wave
@@ -1722,6 +1782,37 @@ __device__ __forceinline__ int operand_words(const ExecMat& M, const Task& w) {
   return load_words(M.pairs + off, n);
 }
 
+// words of task lid and of its operand list
+__device__ __forceinline__ void load_task(const ExecMat& M, int lid, Task& w) {
+  const int wv = load_words(M.tasks + (int64_t)lid * TASK_WORDS, TASK_WORDS);
+#pragma unroll
+  for (int i = 0; i < TASK_WORDS; i++) w.w[i] = word(wv, i);
+  w.pv = operand_words(M, w);
+}
+
+// One successor entry's decrement (Alg. 2 progress update).
+__device__ __forceinline__ void notify_one(const ExecMat& M, int32_t sq) {
+  int32_t dec = 1;
+  if (sq & SUCC_FDEP) {   // an early predecessor of a two-stage wait
+    dec = MERGED_FDEP;
+    sq &= ~SUCC_FDEP;
+  } else if (sq & SUCC_MID) {   // merged DAG: early solve predecessor of a diagonal step
+    dec = SPLIT_W;
+    sq &= ~SUCC_MID;
+  }
+  __hip_atomic_fetch_add(M.remaining + sq, -dec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// per-task trace record
+__device__ __forceinline__ void trace_task(const ExecMat& M, int lid, uint64_t claim, uint64_t start, int type,
+                                           int ticket) {
+  unsigned long long* tr = M.trace + 4 * (int64_t)lid;
+  tr[0] = claim;
+  tr[1] = start;
+  tr[2] = wall_clock64();
+  tr[3] = ((unsigned long long)blockIdx.x << 32) | ((unsigned)type << 24) | ((unsigned)ticket & 0xffffffu);
+}
+
 // The task bodies are inlined into the executor: as functions they saved and
 // restored their registers through scratch memory on every call (360 bytes a
 // lane in the factorization kernel, 556 in the selected inversion).  With
@@ -1738,6 +1829,7 @@ template <int T, int KIND>
 __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat* __restrict__ mats, const int32_t* __restrict__ order,
                                                   int32_t total, ExecCtrl* ctrl, int nrhs, uint64_t limit) {
   constexpr bool SOLVE = KIND == EXEC_SOLVE, SELINV = KIND == EXEC_SELINV, BOTH = KIND == EXEC_FACTOR_SOLVE;
+  constexpr bool FACTOR = !SOLVE && !SELINV;
   // LDS: factorization tasks use S (a tile; POTRF: leading dimension T + 17)
   // and Xi (T x T) or, updates, the whole as a ring; solve tasks only a
   // T x 16 block of Xi; selected-inversion tasks two tiles or
@@ -1765,19 +1857,22 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
       M = mats[mi];
     }
     Task w;
-    {
-      const int wv = load_words(M.tasks + (int64_t)lid * TASK_WORDS, TASK_WORDS);
-#pragma unroll
-      for (int i = 0; i < TASK_WORDS; i++) w.w[i] = word(wv, i);
-    }
-    w.pv = operand_words(M, w);
+    load_task(M, lid, w);
     // the first successors, for the notification
-    const int32_t nsucc = w[6] - w[5];
-    const int succ0 = load_words(M.succ + w[5], nsucc);
+    int32_t nsucc = w[6] - w[5];
+    int succ0 = load_words(M.succ + w[5], nsucc);
     int32_t* cnt = M.remaining + lid;
     uint64_t t_claim = 0, t_start = 0;
     if (M.trace) t_claim = wall_clock64();
     const int type = w[0] & 0xff;
+    // a TRSM of the pivot chain carries the next POTRF with it, whose own
+    // ticket is void
+    if (FACTOR && type == TK_POTRF && (w[0] & TF_CHAIN) != 0) {
+      __syncthreads();
+      if (threadIdx.x == 0) s_ticket = atomicAdd(&ctrl->ticket, 1);
+      __syncthreads();
+      continue;
+    }
     if constexpr (SELINV) selinv_prefetch<T>(M, w, S, Xi);
     // merged factorization + solve DAG: a solve task first waits for its
     // factorization predecessors only (the counter falls below MERGED_FDEP);
@@ -1826,8 +1921,43 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
         case TK_UPDB: task_update_block<T, KIND>(mats + mi, w[0], w[3], w.pv, S, Xi); break;
         case TK_PART: task_update<T>(M, w, 1, S); break;
         case TK_TREE: task_tree<T>(M, w); break;
-        case TK_POTRF: t_start = task_potrf<T>(M, w, S, Xi, cnt, ctrl, limit, ok); break;
-        default: t_start = task_trsm<T>(M, w, S, Xi, cnt, ctrl, limit, ok); break;
+        default: {
+          // TRSM, POTRF, or both (the POTRF is the TRSM's first successor)
+          const bool pair = (w[0] & TF_CHAIN) != 0;
+          bool staged = false;
+          uint64_t t_trsm = 0;
+          Task w2 = w;
+          int lid2 = lid, succ2 = succ0;
+          if (type == TK_TRSM) {
+            if (pair) {
+              lid2 = word(succ0, 0) & ~(SUCC_FDEP | SUCC_MID);
+              load_task(M, lid2, w2);
+              succ2 = load_words(M.succ + w2[5], w2[6] - w2[5]);
+            }
+            t_start = t_trsm = task_trsm<T>(M, w, S, Xi, cnt, ctrl, limit, ok, pair, M.remaining + lid2,
+                                            M.tiles + (int64_t)w2[1] * (T * T), staged);
+            if (!ok || !pair) break;
+          }
+          const int lid1 = lid, w5 = w[5], w7 = w[7], ns1 = nsucc, s1 = succ0;
+          lid = lid2;
+          w = w2;
+          nsucc = w2[6] - w2[5];
+          succ0 = succ2;
+          cnt = M.remaining + lid2;
+          // the TRSM's end, by the last wave (the first one has the panels)
+          auto lead = [&]() INLINE {
+            const int l = thread_id() - (NT - 64);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (l == 0) st_relaxed(M.remaining + lid1, w7);
+            for (int32_t q0 = 0; q0 < ns1; q0 += 64) {
+              const int32_t q = q0 + l;
+              if (l >= 0 && q > 0 && q < ns1) notify_one(M, q0 == 0 ? s1 : gp(M.succ)[w5 + q]);
+            }
+            if (M.trace && l == 0) trace_task(M, lid1, t_claim, t_trsm, TK_TRSM, t);
+          };
+          t_start = task_potrf<T>(M, w, S, Xi, cnt, ctrl, limit, ok, pair, staged, lead);
+          break;
+        }
       }
     }
     if (chain) __builtin_amdgcn_s_setprio(0);
@@ -1858,25 +1988,9 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
     if (threadIdx.x == 0) st_relaxed(cnt, w[7]);   // re-arm for the next launch
     for (int32_t q0 = 0; q0 < nsucc; q0 += 64) {
       const int32_t q = q0 + (int32_t)threadIdx.x;
-      if (threadIdx.x < 64 && q < nsucc) {
-        int32_t sq = q0 == 0 ? succ0 : gp(M.succ)[w[5] + q], dec = 1;
-        if (sq & SUCC_FDEP) {   // an early predecessor of a two-stage wait
-          dec = MERGED_FDEP;
-          sq &= ~SUCC_FDEP;
-        } else if (sq & SUCC_MID) {   // merged DAG: early solve predecessor of a diagonal step
-          dec = SPLIT_W;
-          sq &= ~SUCC_MID;
-        }
-        __hip_atomic_fetch_add(M.remaining + sq, -dec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      if (threadIdx.x < 64 && q < nsucc) notify_one(M, q0 == 0 ? succ0 : gp(M.succ)[w[5] + q]);
     }
-    if (M.trace && threadIdx.x == 0) {
-      unsigned long long* tr = M.trace + 4 * (int64_t)lid;
-      tr[0] = t_claim;
-      tr[1] = t_start;
-      tr[2] = wall_clock64();
-      tr[3] = ((unsigned long long)blockIdx.x << 32) | ((unsigned)type << 24) | ((unsigned)t & 0xffffffu);
-    }
+    if (M.trace && threadIdx.x == 0) trace_task(M, lid, t_claim, t_start, w[0] & 0xff, t);
   }
   // the last workgroup to leave re-arms the control block; after an abort it
   // also re-arms every progress counter of the launch (skipped tasks did not

@@ -45,6 +45,7 @@ enum TaskFlag : int32_t {
   TF_ACC = 1 << 10,   // PART: P_s += sum (continues a chain) instead of P_s = sum
   TF_SPLIT = 1 << 11, // POTRF/TRSM/FDIAG/BDIAG: two-stage wait (early predecessors, then the chain one)
   TF_ARROW = 1 << 12, // PART: partial of an arrow-corner tile (FP64 in mixed mode)
+  TF_CHAIN = 1 << 13, // TRSM with the POTRF it is the late predecessor of (its first successor), that POTRF
 };
 
 // One task = 8 int32.
@@ -87,7 +88,9 @@ constexpr int32_t SIG_TRANS = 1 << 30;
 // late one the POTRF of its column, so it prefetches its tile and does its
 // fused product before the POTRF ends; a POTRF with a fused product waits
 // late for the TRSM of that operand (the panel of the previous column) and
-// prefetches its tile before.
+// prefetches its tile before.  Where every early predecessor of such a POTRF
+// has an earlier ticket than that TRSM (TF_CHAIN on both), the TRSM's
+// workgroup runs the POTRF next and the TRSM does not decrement its counter.
 // Solve DAG (TF_SPLIT): a diagonal step with two fused products waits late
 // for the step that solves the block of its second product (the previous
 // step of the chain) and does the product with the other one before.  In
