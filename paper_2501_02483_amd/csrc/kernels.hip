@@ -78,25 +78,32 @@ __device__ __forceinline__ void st_dev(GLOBAL float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_dev(double* p, double v) { st_dev(gp(p), v); }
-// The same for 16 bytes of a tile (an atomic store has at most 8): a buffer
+// The same for 16 bytes of a tile or vector block (an atomic store has at most 8): a buffer
 // store, whose cache policy is an operand.  As inline asm the compiler would
 // not count it, and a later wait for loads issued before it would wait for
 // the store too.
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
-template <int T>
-struct DevTile {
+struct DevBlock {
   __amdgpu_buffer_rsrc_t rsrc;
-  __device__ __forceinline__ explicit DevTile(double* tile)
-      : rsrc(__builtin_amdgcn_make_buffer_rsrc(tile, 0, T * T * 8, 0x00020000)) {}
-  // element e and the next one, e even
+  __device__ __forceinline__ DevBlock(double* block, int64_t bytes)
+      : rsrc(__builtin_amdgcn_make_buffer_rsrc(block, 0, (int)bytes, 0x00020000)) {}
+  // elements e and e + 1, e even
   __device__ __forceinline__ void store(int e, v2d v) const {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rsrc, 8 * e, 0, /* sc1 */ 16);
+  }
+  __device__ __forceinline__ void store(int e, v4d v) const {
+    store(e, v2d{v[0], v[1]});
+    store(e + 2, v2d{v[2], v[3]});
   }
   __device__ __forceinline__ void store(int e, double v) const {
     typedef unsigned v2u __attribute__((ext_vector_type(2)));
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), rsrc, 8 * e, 0, /* sc1 */ 16);
   }
+};
+template <int T>
+struct DevTile : DevBlock {
+  __device__ __forceinline__ explicit DevTile(double* tile) : DevBlock(tile, T * T * 8) {}
 };
 
 // ------------------------------------------------------------------ helpers
@@ -1009,53 +1016,77 @@ __device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, 
 // vector block, as 16 x 16 x 4 FP64 MFMA products with the right-hand sides
 // padded to 16 columns.
 // MFMA operands are read from global memory straight into registers.  At
-// MFMA step s the four k-groups of the 16 x 16 x 4 instruction (lane >> 4 =
-// g) take k = (T/4) g + s, so that one lane's operands are contiguous: the
-// B operand (vector block, column lane & 15) is one run of T/4 doubles, and
-// so is the A operand of a transposed tile (backward sweep: A(r, k) =
-// L(k, r), a piece of column r); a direct tile (forward sweep) is read as
-// T/4 loads whose 16 lanes cover 16 consecutive rows.  Wave w owns rows
-// 16 w .. 16 w + 15 of the T x 16 result (waves past T/16 idle).
+// MFMA steps 2 s and 2 s + 1 the four k-groups of the 16 x 16 x 4 instruction
+// (lane >> 4 = g) take k = 8 s + 2 g and the next one: a 16-byte load per lane
+// for the B operand (vector block, column lane & 15) and for the A operand of
+// a transposed tile (backward sweep: A(r, k) = L(k, r), a piece of column r),
+// 64 bytes of each of 16 columns per load (a run of T/4 doubles per lane
+// instead touches 64 lines per load: 16-RHS solve of the n = 200,000
+// variable-band matrix 2.36 -> 2.17 ms, a residual pass at n = 500,000 3.28 ->
+// 2.64 ms); a direct tile (forward sweep) is read as T/4 loads whose 16 lanes
+// cover 16 consecutive rows.  Wave w owns rows 16 w .. 16 w + 15 of the T x 16
+// result (waves past T/16 idle), in an order of A's rows that leaves each lane
+// four consecutive ones of its column: 16-byte accesses to the vector blocks
+// (2.17 -> 2.12 ms).
 template <int T>
 struct SolveOps {
   static constexpr int NS = T / 4;   // MFMA steps per tile
+  // leading dimension of a block in LDS: the 16-byte reads of 16 columns
+  // cover all banks
+  static constexpr int LDV = T + 2;
+  // row of A's lane: result register r of lane group g is then row 4 g + r
+  static __device__ __forceinline__ int a_row(int wave, int lane) {
+    return 16 * wave + 4 * (lane & 3) + ((lane & 15) >> 2);
+  }
+  // this lane's first element of a T x 16 block with leading dimension ld
+  static __device__ __forceinline__ int elem(int wave, int lane, int ld) {
+    return 16 * wave + 4 * (lane >> 4) + (lane & 15) * ld;
+  }
+  // its four elements of a vector block in global memory
+  static __device__ __forceinline__ v4d load_c(const double* V, int e, bool ok) {
+    const GLOBAL d2* p = (const GLOBAL d2*)(V + e);
+    const d2 lo = ok ? p[0] : d2{0.0, 0.0}, hi = ok ? p[1] : d2{0.0, 0.0};
+    return v4d{lo.x, lo.y, hi.x, hi.y};
+  }
+  // k of MFMA step s in lane group g
+  static __device__ __forceinline__ int k_of(int s, int g) { return 8 * (s >> 1) + 2 * g + (s & 1); }
   typedef double d2 __attribute__((ext_vector_type(2)));
-  // A operand of tile Lt for rows 16 w + (lane & 15)
+  // A operand of tile Lt
   static __device__ __forceinline__ void load_a(double (&a)[NS], const double* Lt, bool trans, int wave, int lane) {
-    const int r = 16 * wave + (lane & 15), g = lane >> 4;
+    const int r = a_row(wave, lane), g = lane >> 4;
     if (trans) {
-      const GLOBAL d2* p = (const GLOBAL d2*)(Lt + NS * g + (int64_t)r * T);
+      const GLOBAL d2* p = (const GLOBAL d2*)(Lt + 2 * g + (int64_t)r * T);
 #pragma unroll
       for (int q = 0; q < NS / 2; q++) {
-        const d2 v = p[q];
+        const d2 v = p[4 * q];
         a[2 * q] = v.x;
         a[2 * q + 1] = v.y;
       }
     } else {
-      const GLOBAL double* p = gp(Lt) + r + (int64_t)NS * g * T;
+      const GLOBAL double* p = gp(Lt) + r + 2 * g * T;
 #pragma unroll
-      for (int q = 0; q < NS; q++) a[q] = p[(int64_t)q * T];
+      for (int q = 0; q < NS; q++) a[q] = p[k_of(q, 0) * T];
     }
   }
   // B operand of a vector block (T x nrhs, leading dimension T) in global memory
   static __device__ __forceinline__ void load_b(double (&b)[NS], const double* V, int nrhs, int lane) {
     const int j = lane & 15, g = lane >> 4;
-    const GLOBAL d2* p = (const GLOBAL d2*)(V + NS * g + (int64_t)j * T);
+    const GLOBAL d2* p = (const GLOBAL d2*)(V + 2 * g + (int64_t)j * T);
     const bool ok = j < nrhs;
 #pragma unroll
     for (int q = 0; q < NS / 2; q++) {
-      const d2 v = ok ? p[q] : d2{0.0, 0.0};
+      const d2 v = ok ? p[4 * q] : d2{0.0, 0.0};
       b[2 * q] = v.x;
       b[2 * q + 1] = v.y;
     }
   }
-  // the same from a T x 16 block in LDS
+  // the same from a T x 16 block in LDS (leading dimension LDV)
   static __device__ __forceinline__ void load_b_lds(double (&b)[NS], const double* V, int lane) {
     const int j = lane & 15, g = lane >> 4;
-    const d2* p = (const d2*)(V + NS * g + j * T);
+    const d2* p = (const d2*)(V + 2 * g + j * LDV);
 #pragma unroll
     for (int q = 0; q < NS / 2; q++) {
-      const d2 v = p[q];
+      const d2 v = p[4 * q];
       b[2 * q] = v.x;
       b[2 * q + 1] = v.y;
     }
@@ -1100,10 +1131,10 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
   const double* vsrc = fwd ? M.vy : M.vz;
   const int np = w[3] - w[2];
   const int pv = w.pv;
-  // output element of this lane, register r: row 16 wave + (lane >> 4) + 4 r, column lane & 15
-  const int col = lane & 15;
+  // this lane's four output elements
+  const int col = lane & 15, el = O::elem(wave, lane, T);
   const double* base = fwd ? M.vy + m * vb : ((w[0] & TF_FIRST) ? M.vy + m * vb : M.vz + m * vb);
-  GLOBAL double* dst = gp(fwd ? M.vy + m * vb : M.vz + m * vb);
+  const DevBlock dst(fwd ? M.vy + m * vb : M.vz + m * vb, vb * 8);
   v4d acc = v4d{0.0, 0.0, 0.0, 0.0};
   if (diag) {
     // static operands first (at most two fused products), then the wait
@@ -1117,14 +1148,10 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
     if (ok) ok = wait_below(cnt, split ? (K == EXEC_FACTOR_SOLVE ? SPLIT_W : MERGED_FDEP) : 1, ctrl, limit);
     if (!ok) return 0;
     uint64_t t_start = M.trace ? wall_clock64() : 0;
-    double bs[4];
+    v4d bs;
     if (act) {
       if (np > 0) O::load_b(b0, vsrc + word(pv, 1) * vb, nrhs, lane);
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int row = 16 * wave + (lane >> 4) + 4 * r;
-        bs[r] = col < nrhs ? gp(base)[row + col * T] : 0.0;
-      }
+      bs = O::load_c(base, el, col < nrhs);
       if (np > 0) acc = O::mma(acc, a0, b0);
     }
     if (split) {
@@ -1138,54 +1165,49 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
         O::load_b(b1, vsrc + word(pv, 3) * vb, nrhs, lane);
         acc = O::mma(acc, a1, b1);
       }
-      // base - acc into LDS (T x 16, leading dimension T) for the product
-      // with the inverse diagonal tile
-#pragma unroll
-      for (int r = 0; r < 4; r++) LV[(16 * wave + (lane >> 4) + 4 * r) + col * T] = bs[r] - acc[r];
+      // base - acc into LDS for the product with the inverse diagonal tile
+      const v4d z = bs - acc;
+      v2d* l = reinterpret_cast<v2d*>(LV + O::elem(wave, lane, O::LDV));
+      l[0] = v2d{z[0], z[1]};
+      l[1] = v2d{z[2], z[3]};
     }
     __syncthreads();
     if (act) {
       O::load_b_lds(b0, LV, lane);
       const v4d out = O::mma(v4d{0.0, 0.0, 0.0, 0.0}, ai, b0);
-      if (col < nrhs) {
-#pragma unroll
-        for (int r = 0; r < 4; r++) st_dev(dst + (16 * wave + (lane >> 4) + 4 * r) + col * T, out[r]);
-      }
+      if (col < nrhs) dst.store(el, out);
     }
     return t_start;
   }
-  // a chunk of products: the factor tiles of the first two pairs are read
-  // before the wait; then two pairs stay in flight (the operands of pair
-  // p + 2 are loaded while pair p + 1 is multiplied)
-  double a[2][NS], b[2][NS], bs[4];
-  if (act && np > 0) {
-    O::load_a(a[0], M.tiles + (int64_t)word(pv, 0) * TT, !fwd, wave, lane);
-    if (np > 1) O::load_a(a[1], M.tiles + (int64_t)word(pv, 2) * TT, !fwd, wave, lane);
+  // a chunk of products: the factor tiles of the first NF pairs are read
+  // before the wait; then NF pairs stay in flight (the operands of pair
+  // p + NF are loaded once pair p has been multiplied).  Three take all
+  // registers: the solve of the n = 200,000 variable-band matrix 1.97 -> 1.93
+  // ms, but the merged launch 0.7 % slower, which keeps two.
+  constexpr int NF = K == EXEC_SOLVE ? 3 : 2;
+  double a[NF][NS], b[NF][NS];
+  v4d bs;
+  if (act) {
+#pragma unroll
+    for (int u = 0; u < NF; u++)
+      if (u < np) O::load_a(a[u], M.tiles + (int64_t)word(pv, 2 * u) * TT, !fwd, wave, lane);
   }
   if (ok) ok = wait_below(cnt, 1, ctrl, limit);
   if (!ok) return 0;
   const uint64_t t_start = M.trace ? wall_clock64() : 0;
   if (act) {
-    if (np > 0) O::load_b(b[0], vsrc + word(pv, 1) * vb, nrhs, lane);
-    if (np > 1) O::load_b(b[1], vsrc + word(pv, 3) * vb, nrhs, lane);
-    if (type != TK_FPART) {
 #pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const int row = 16 * wave + (lane >> 4) + 4 * r;
-        bs[r] = col < nrhs ? gp(base)[row + col * T] : 0.0;
-      }
-    }
-    for (int p = 0; p < np; p += 2) {
-      acc = O::mma(acc, a[0], b[0]);
-      if (p + 2 < np) {
-        O::load_a(a[0], M.tiles + (int64_t)word(pv, 2 * p + 4) * TT, !fwd, wave, lane);
-        O::load_b(b[0], vsrc + word(pv, 2 * p + 5) * vb, nrhs, lane);
-      }
-      if (p + 1 < np) {
-        acc = O::mma(acc, a[1], b[1]);
-        if (p + 3 < np) {
-          O::load_a(a[1], M.tiles + (int64_t)word(pv, 2 * p + 6) * TT, !fwd, wave, lane);
-          O::load_b(b[1], vsrc + word(pv, 2 * p + 7) * vb, nrhs, lane);
+    for (int u = 0; u < NF; u++)
+      if (u < np) O::load_b(b[u], vsrc + word(pv, 2 * u + 1) * vb, nrhs, lane);
+    if (type != TK_FPART) bs = O::load_c(base, el, col < nrhs);
+    for (int p = 0; p < np; p += NF) {
+#pragma unroll
+      for (int u = 0; u < NF; u++) {
+        if (p + u < np) acc = O::mma(acc, a[u], b[u]);
+        if (p + u + NF < np) {
+          const int q = 2 * (p + u + NF);
+          O::load_a(a[u], M.tiles + (int64_t)word(pv, q) * TT, !fwd, wave, lane);
+          O::load_b(b[u], vsrc + word(pv, q + 1) * vb, nrhs, lane);
         }
       }
     }
@@ -1193,41 +1215,70 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
   if (!act) return t_start;
   if (type == TK_FPART) {
     // one chunk of a long row: the partial product into its slot
-    GLOBAL double* q = gp(M.vpart + (int64_t)w[4] * vb);
-    if (col < nrhs) {
-#pragma unroll
-      for (int r = 0; r < 4; r++) st_dev(q + (16 * wave + (lane >> 4) + 4 * r) + col * T, acc[r]);
-    }
+    if (col < nrhs) DevBlock(M.vpart + (int64_t)w[4] * vb, vb * 8).store(el, acc);
     return t_start;
   }
-  if (col < nrhs) {
-#pragma unroll
-    for (int r = 0; r < 4; r++) st_dev(dst + (16 * wave + (lane >> 4) + 4 * r) + col * T, bs[r] - acc[r]);
-  }
+  if (col < nrhs) dst.store(el, bs - acc);
   return t_start;
 }
 
 // Y_m -= Q_a + ... + Q_(b-1): the partial products of a long row, summed in
-// a fixed order (so the result does not depend on the schedule)
+// a fixed order (so the result does not depend on the schedule): four running
+// sums, slot q in sum (q - a) mod 4.  The task is on the chain of the
+// separators' steps and waits for memory only: eight slots are in flight for
+// every pair of elements, and all pairs of a lane at once (four slots of one
+// element at a time: 9.4 us a task, now 4.2; the solve above 2.12 -> 1.96 ms).
+template <int T, int NP>   // NP: pairs of elements per lane
+__device__ __forceinline__ void fsum_pairs(const double* part, double* y, int n, int64_t vb) {
+  const int e = 2 * thread_id();
+  const int ne = (int)vb;
+  v2d sum[NP][4], base[NP];
+#pragma unroll
+  for (int p = 0; p < NP; p++) {
+    const int x = e + 2 * NT * p;
+    base[p] = x < ne ? *(const GLOBAL v2d*)(y + x) : v2d{0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < 4; j++) sum[p][j] = v2d{0.0, 0.0};
+  }
+  int q = 0;
+  for (; q + 4 <= n; q += 8) {
+    v2d v[NP][8];
+    const bool two = q + 8 <= n;
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+#pragma unroll
+      for (int p = 0; p < NP; p++) {
+        const int x = e + 2 * NT * p;
+        v[p][j] = x < ne && (j < 4 || two) ? *(const GLOBAL v2d*)(part + (q + j) * vb + x) : v2d{0.0, 0.0};
+      }
+#pragma unroll
+    for (int j = 0; j < 8; j++)
+#pragma unroll
+      for (int p = 0; p < NP; p++)
+        if (j < 4 || two) sum[p][j & 3] += v[p][j];
+    if (!two) {
+      q += 4;
+      break;
+    }
+  }
+  for (; q < n; q++)
+#pragma unroll
+    for (int p = 0; p < NP; p++) {
+      const int x = e + 2 * NT * p;
+      if (x < ne) sum[p][0] += *(const GLOBAL v2d*)(part + q * vb + x);
+    }
+  const DevBlock dst(y, vb * 8);
+#pragma unroll
+  for (int p = 0; p < NP; p++) {
+    const int x = e + 2 * NT * p;
+    if (x < ne) dst.store(x, base[p] - ((sum[p][0] + sum[p][1]) + (sum[p][2] + sum[p][3])));
+  }
+}
+
 template <int T>
 __device__ __forceinline__ void task_fsum(const ExecMat& M, const Task& w, int nrhs) {
-  const int64_t vb = (int64_t)T * nrhs;
-  double* y = M.vy + (int64_t)w[1] * vb;
-  const int a = w[2], b = w[3];
-  for (int e = thread_id(); e < T * nrhs; e += NT) {
-    // four running sums (slot q goes to sum q mod 4) keep four loads in
-    // flight; the order is fixed, so the result does not depend on timing
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int q = a;
-    for (; q + 4 <= b; q += 4) {
-      s0 += M.vpart[(int64_t)q * vb + e];
-      s1 += M.vpart[(int64_t)(q + 1) * vb + e];
-      s2 += M.vpart[(int64_t)(q + 2) * vb + e];
-      s3 += M.vpart[(int64_t)(q + 3) * vb + e];
-    }
-    for (; q < b; q++) s0 += M.vpart[(int64_t)q * vb + e];
-    st_dev(y + e, y[e] - ((s0 + s1) + (s2 + s3)));
-  }
+  const int64_t vb = (int64_t)T * nrhs;   // even, at most 16 T
+  fsum_pairs<T, 16 * T / (2 * NT)>(M.vpart + w[2] * vb, M.vy + (int64_t)w[1] * vb, w[3] - w[2], vb);
 }
 
 // ------------------------------------------------------- selected inversion
@@ -1835,7 +1886,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
   // T x 16 block of Xi; selected-inversion tasks two tiles or
   // the ring.
   constexpr int NS = SOLVE ? 2 : SELINV ? T * T : T * (T + 17);
-  constexpr int NX = SOLVE ? T * 16 : T * T;
+  constexpr int NX = SOLVE ? SolveOps<T>::LDV * 16 : T * T;
   constexpr int NR = SOLVE ? 0 : Ring<T, double>::NST * 2 * Ring<T, double>::HB / 8;
   __shared__ __attribute__((aligned(1024))) double S[NS + NX > NR ? NS + NX : NR];
   double* const Xi = S + NS;
@@ -2568,7 +2619,7 @@ __global__ __launch_bounds__(NT) void residual_mma_kernel(const double* __restri
   const int m = items[4 * q], kind = items[4 * q + 1], lo = items[4 * q + 2], hi = items[4 * q + 3];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const bool act = 16 * wave < T;
-  const int col = lane & 15, g = lane >> 4, r = 16 * wave + (lane & 15);
+  const int col = lane & 15, g = lane >> 4, r = O::a_row(wave, lane);
   const int64_t vb = (int64_t)T * nrhs;
   const int ncol = absmode ? 1 : nrhs;
   const bool trans = kind == 1;
@@ -2605,7 +2656,7 @@ __global__ __launch_bounds__(NT) void residual_mma_kernel(const double* __restri
       O::load_a(at, orig + (int64_t)tile * TT, true, wave, lane);
 #pragma unroll
       for (int s = 0; s < NS; s++) {
-        const double v = NS * g + s == r ? 0.0 : at[s];
+        const double v = O::k_of(s, g) == r ? 0.0 : at[s];
         at[s] = absmode ? fabs(v) : v;
         if (apart && !absmode) rs += fabs(v);
       }
@@ -2623,8 +2674,9 @@ __global__ __launch_bounds__(NT) void residual_mma_kernel(const double* __restri
   }
   double* out = part + (int64_t)q * vb;
   if (col < ncol) {
-#pragma unroll
-    for (int rr = 0; rr < 4; rr++) out[(16 * wave + (lane >> 4) + 4 * rr) + col * T] = acc[rr];
+    v2d* o = reinterpret_cast<v2d*>(out + O::elem(wave, lane, T));
+    o[0] = v2d{acc[0], acc[1]};
+    o[1] = v2d{acc[2], acc[3]};
   }
   if (apart) {
     // the four lanes of a row (k groups g = 0..3) hold its whole sum
