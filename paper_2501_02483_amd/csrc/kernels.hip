@@ -117,16 +117,6 @@ __device__ __forceinline__ void st_relaxed(int32_t* p, int32_t v) {
 __device__ __forceinline__ void fence_acquire() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
 __device__ __forceinline__ void fence_release() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent"); }
 
-// 1/sqrt(d): hardware estimate, then one third-order correction
-// y = y0 (1 + e/2 + 3 e^2 / 8), e = 1 - d y0^2 (four dependent FP64 steps
-// instead of six for two Newton steps; the estimate's error is cubed)
-__device__ __forceinline__ double rsqrt_c(double d) {
-  const double y0 = __builtin_amdgcn_rsq(d);
-  const double e = fma(-d * y0, y0, 1.0);
-  const double p = fma(0.375, e, 0.5);
-  return fma(y0 * e, p, y0);
-}
-
 // ------------------------------------------------------- tile products (MFMA)
 // 16 x 16 x 4 products: lane l holds A[l & 15][l >> 4], B[l >> 4][l & 15] and,
 // in register r of the result, D[col(l, r)][l & 15].  The A operand is taken
@@ -817,9 +807,11 @@ __device__ __forceinline__ void deferred_slot(double (&D)[16], double (&a)[16]) 
 }
 
 // Column J of a panel: d[J] the pivot, D the diagonal block's rows (one per
-// lane of each 16-lane row), a one further row per lane.  The steps of
-// 1/sqrt(d) (rsqrt_c) depend on each other: the previous column's deferred
-// updates go between them.
+// lane of each 16-lane row), a one further row per lane.  1/sqrt(d) is the
+// hardware's estimate y0 with one third-order correction, y0 (1 + e/2 +
+// 3 e^2 / 8), e = 1 - d y0^2 (four dependent steps instead of six for two
+// Newton steps; the estimate's error is cubed).  Its steps depend on each
+// other: the previous column's deferred updates go between them.
 template <int J>
 __device__ __forceinline__ void panel_column(double (&D)[16], double (&a)[16], double (&d)[16]) {
   const double y0 = __builtin_amdgcn_rsq(d[J]);
