@@ -164,16 +164,21 @@ struct TileStage {
 
 // ------------------------------------------------------------ task bodies
 
+struct Wait {
+  ExecCtrl* ctrl;
+  uint64_t limit;
+  int32_t* flag;   // in LDS
+};
+
 // The calling workgroup waits until *cnt < bound (all predecessors, or all
 // predecessors of one kind, have finished), then acquires.  Wave 0 polls.
 // The wait is bounded: it gives up when another workgroup of the launch has
 // given up (ctrl->abort) or when `limit` ticks of the 100 MHz wall clock pass
 // without the counter falling; the first to give up sets ctrl->abort.  The
 // result is the same for every thread (false: gave up).  The outcome goes
-// through LDS; the second barrier keeps a later wait from overwriting it
-// before every wave has read it.
-__device__ __forceinline__ bool wait_below(int32_t* cnt, int32_t bound, ExecCtrl* ctrl, uint64_t limit) {
-  __shared__ int32_t s_ok;
+// through LDS (flag); the second barrier keeps a later wait from overwriting
+// it before every wave has read it.
+__device__ __forceinline__ bool wait_below(int32_t* cnt, int32_t bound, const Wait& wt) {
   if (thread_id() < 64) {
     int32_t ok = 1;
     if (__builtin_amdgcn_readfirstlane(ld_relaxed(cnt)) >= bound) {
@@ -181,31 +186,29 @@ __device__ __forceinline__ bool wait_below(int32_t* cnt, int32_t bound, ExecCtrl
       for (;;) {
         __builtin_amdgcn_s_sleep(1);
         if (__builtin_amdgcn_readfirstlane(ld_relaxed(cnt)) < bound) break;
-        if (__builtin_amdgcn_readfirstlane(ld_relaxed(&ctrl->abort)) != 0) {
+        if (__builtin_amdgcn_readfirstlane(ld_relaxed(&wt.ctrl->abort)) != 0) {
           ok = 0;
           break;
         }
-        if (wall_clock64() - t0 > limit) {
-          st_relaxed(&ctrl->abort, 1);
+        if (wall_clock64() - t0 > wt.limit) {
+          st_relaxed(&wt.ctrl->abort, 1);
           ok = 0;
           break;
         }
       }
     }
     fence_acquire();
-    if (thread_id() == 0) s_ok = ok;
+    if (thread_id() == 0) *wt.flag = ok;
   }
   __syncthreads();
-  const bool ok = __builtin_amdgcn_readfirstlane(s_ok) != 0;
+  const bool ok = __builtin_amdgcn_readfirstlane(*wt.flag) != 0;
   __syncthreads();
   return ok;
 }
 
 // Waits until *a < ba (the answer 1) or, failing that, *b < bb (2); 0 if the
 // launch is abandoned.
-__device__ __forceinline__ int wait_first(int32_t* a, int32_t ba, int32_t* b, int32_t bb, ExecCtrl* ctrl,
-                                          uint64_t limit) {
-  __shared__ int32_t s_which;
+__device__ __forceinline__ int wait_first(int32_t* a, int32_t ba, int32_t* b, int32_t bb, const Wait& wt) {
   if (thread_id() < 64) {
     int32_t which = 0;
     const uint64_t t0 = wall_clock64();
@@ -214,18 +217,18 @@ __device__ __forceinline__ int wait_first(int32_t* a, int32_t ba, int32_t* b, in
       if (__builtin_amdgcn_readfirstlane(va) < ba) which = 1;
       else if (__builtin_amdgcn_readfirstlane(vb) < bb) which = 2;
       if (which != 0) break;
-      if (__builtin_amdgcn_readfirstlane(ld_relaxed(&ctrl->abort)) != 0) break;
-      if (wall_clock64() - t0 > limit) {
-        st_relaxed(&ctrl->abort, 1);
+      if (__builtin_amdgcn_readfirstlane(ld_relaxed(&wt.ctrl->abort)) != 0) break;
+      if (wall_clock64() - t0 > wt.limit) {
+        st_relaxed(&wt.ctrl->abort, 1);
         break;
       }
       __builtin_amdgcn_s_sleep(1);
     }
     fence_acquire();
-    if (thread_id() == 0) s_which = which;
+    if (thread_id() == 0) *wt.flag = which;
   }
   __syncthreads();
-  const int which = __builtin_amdgcn_readfirstlane(s_which);
+  const int which = __builtin_amdgcn_readfirstlane(*wt.flag);
   __syncthreads();
   return which;
 }
@@ -249,7 +252,7 @@ struct Ring {
   static constexpr int HB = T * KS * (int)sizeof(E);               // bytes of one operand's stage
   static constexpr int NI = 2 * HB / 4096;                         // 1 KB transfers per wave and stage
   static constexpr int NST = T == 64 ? 4 : 3;                      // slots (64 KB; 48 KB at T = 32)
-  static_assert(NST * 2 * HB <= 65536, "transfers address LDS below 64 KB");
+  static_assert(NST * 2 * HB <= 65536, "transfers address LDS below 64 KB, the ring starts at 0 (ExecLds)");
 };
 
 // 1 KB from base + voff (voff per lane) to LDS at lds + 16 lane.  No register
@@ -664,14 +667,14 @@ __device__ __forceinline__ void stage_diag(const double* C, double* S) {
 // first.
 template <int T>
 __device__ __forceinline__ uint64_t task_trsm(const ExecMat& M, const Task& w, double* LX, double* LY, int32_t* cnt,
-                                              ExecCtrl* ctrl, uint64_t limit, bool& ok, bool chain, int32_t* next,
-                                              const double* C2, bool& staged) {
+                                              const Wait& wt, bool& ok, bool chain, int32_t* next, const double* C2,
+                                              bool& staged) {
   constexpr int TT = T * T, NB = T / 16, NC = NB == 4 ? 4 : 1;   // NC: result blocks per wave
   const int lane = thread_id() & 63, li = lane & 15, lk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(thread_id() >> 6);
   const int r0 = 16 * (wave % NB), cb0 = NB == 4 ? 0 : wave / NB;
   const bool split = (w[0] & TF_SPLIT) != 0;
-  if (ok) ok = wait_below(cnt, split ? MERGED_FDEP : 1, ctrl, limit);
+  if (ok) ok = wait_below(cnt, split ? MERGED_FDEP : 1, wt);
   if (!ok) return 0;
   uint64_t t_start = M.trace ? wall_clock64() : 0;
   const int nf = w[4] - w[3];
@@ -705,14 +708,14 @@ __device__ __forceinline__ uint64_t task_trsm(const ExecMat& M, const Task& w, d
   if (split) {
     // the POTRF of the column: its inverse is the last operand
     if (chain) {
-      const int which = wait_first(next, 2, cnt, 1, ctrl, limit);
+      const int which = wait_first(next, 2, cnt, 1, wt);
       ok = which != 0;
       if (which == 1) {
         stage_diag<T>(C2, LX);
         staged = true;
       }
     }
-    if (ok) ok = wait_below(cnt, 1, ctrl, limit);
+    if (ok) ok = wait_below(cnt, 1, wt);
     if (!ok) return 0;
     if (M.trace) t_start = wall_clock64();
   }
@@ -850,8 +853,7 @@ __device__ __forceinline__ void panel_column(double (&D)[16], double (&a)[16], d
 // n = 10,000, w = 64, natural order 2.82 -> 2.64 ms, 1,000 rows 279 -> 258 us.
 template <int T, class Lead>
 __device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, double* S, double* Xi, int32_t* cnt,
-                                               ExecCtrl* ctrl, uint64_t limit, bool& ok, bool chain, bool staged,
-                                               Lead&& lead) {
+                                               const Wait& wt, bool& ok, bool chain, bool staged, Lead&& lead) {
   constexpr int TT = T * T, NBK = T / 16, LD = T + 17;
   const int tid = thread_id(), lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -865,12 +867,12 @@ __device__ __forceinline__ uint64_t task_potrf(const ExecMat& M, const Task& w, 
   const bool fused = w[4] > w[3];
   if (!staged) {
     // (the TRSM it follows does not decrement the counter)
-    ok = wait_below(cnt, chain ? 2 : split ? MERGED_FDEP : 1, ctrl, limit);
+    ok = wait_below(cnt, chain ? 2 : split ? MERGED_FDEP : 1, wt);
     if (!ok) return 0;
     stage_diag<T>(C, S);
   }
   if (split && !chain) {
-    ok = wait_below(cnt, 1, ctrl, limit);
+    ok = wait_below(cnt, 1, wt);
     if (!ok) return 0;
   }
   const uint64_t t_start = M.trace ? wall_clock64() : 0;
@@ -1110,7 +1112,7 @@ struct SolveOps {
 // when this task's own wait gave up; the task then writes nothing.
 template <int T, int K>
 __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w, int nrhs, int32_t* cnt,
-                                                 double* LV, ExecCtrl* ctrl, uint64_t limit, bool& ok) {
+                                                 double* LV, const Wait& wt, bool& ok) {
   typedef SolveOps<T> O;
   constexpr int TT = T * T, NS = O::NS;
   const int type = w[0] & 0xff;
@@ -1137,7 +1139,7 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
       if (np > 1) O::load_a(a1, M.tiles + (int64_t)word(pv, 2) * TT, !fwd, wave, lane);
       O::load_a(ai, M.linv + (int64_t)m * TT, !fwd, wave, lane);
     }
-    if (ok) ok = wait_below(cnt, split ? (K == EXEC_FACTOR_SOLVE ? SPLIT_W : MERGED_FDEP) : 1, ctrl, limit);
+    if (ok) ok = wait_below(cnt, split ? (K == EXEC_FACTOR_SOLVE ? SPLIT_W : MERGED_FDEP) : 1, wt);
     if (!ok) return 0;
     uint64_t t_start = M.trace ? wall_clock64() : 0;
     v4d bs;
@@ -1148,7 +1150,7 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
     }
     if (split) {
       // the previous step of the chain: its block is the second operand
-      ok = wait_below(cnt, 1, ctrl, limit);
+      ok = wait_below(cnt, 1, wt);
       if (!ok) return 0;
       if (M.trace) t_start = wall_clock64();
     }
@@ -1184,7 +1186,7 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
     for (int u = 0; u < NF; u++)
       if (u < np) O::load_a(a[u], M.tiles + (int64_t)word(pv, 2 * u) * TT, !fwd, wave, lane);
   }
-  if (ok) ok = wait_below(cnt, 1, ctrl, limit);
+  if (ok) ok = wait_below(cnt, 1, wt);
   if (!ok) return 0;
   const uint64_t t_start = M.trace ? wall_clock64() : 0;
   if (act) {
@@ -1856,6 +1858,23 @@ __device__ __forceinline__ void trace_task(const ExecMat& M, int lid, uint64_t c
   tr[3] = ((unsigned long long)blockIdx.x << 32) | ((unsigned)type << 24) | ((unsigned)ticket & 0xffffffu);
 }
 
+// LDS of the executor: factorization tasks use S (a tile; POTRF: leading
+// dimension T + 17) and Xi (T x T) or, updates, the whole as a ring; solve
+// tasks only a T x 16 block of Xi; selected-inversion tasks two tiles or the
+// ring.  One object, so that the ring, whose transfers address LDS below
+// 64 KB, starts at LDS address 0 whatever else the kernel keeps there.
+template <int T, int KIND>
+struct ExecLds {
+  static constexpr bool SOLVE = KIND == EXEC_SOLVE;
+  static constexpr int NS = SOLVE ? 2 : KIND == EXEC_SELINV ? T * T : T * (T + 17);
+  static constexpr int NX = SOLVE ? SolveOps<T>::LDV * 16 : T * T;
+  static constexpr int NR = SOLVE ? 0 : Ring<T, double>::NST * 2 * Ring<T, double>::HB / 8;
+  double S[NS + NX > NR ? NS + NX : NR];
+  int32_t ticket;   // the next task
+  int32_t flag;     // the outcome of a wait
+  int32_t last;     // the last workgroup to leave
+};
+
 // The task bodies are inlined into the executor: as functions they saved and
 // restored their registers through scratch memory on every call (360 bytes a
 // lane in the factorization kernel, 556 in the selected inversion).  With
@@ -1873,25 +1892,21 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
                                                   int32_t total, ExecCtrl* ctrl, int nrhs, uint64_t limit) {
   constexpr bool SOLVE = KIND == EXEC_SOLVE, SELINV = KIND == EXEC_SELINV, BOTH = KIND == EXEC_FACTOR_SOLVE;
   constexpr bool FACTOR = !SOLVE && !SELINV;
-  // LDS: factorization tasks use S (a tile; POTRF: leading dimension T + 17)
-  // and Xi (T x T) or, updates, the whole as a ring; solve tasks only a
-  // T x 16 block of Xi; selected-inversion tasks two tiles or
-  // the ring.
-  constexpr int NS = SOLVE ? 2 : SELINV ? T * T : T * (T + 17);
-  constexpr int NX = SOLVE ? SolveOps<T>::LDV * 16 : T * T;
-  constexpr int NR = SOLVE ? 0 : Ring<T, double>::NST * 2 * Ring<T, double>::HB / 8;
-  __shared__ __attribute__((aligned(1024))) double S[NS + NX > NR ? NS + NX : NR];
-  double* const Xi = S + NS;
-  __shared__ int32_t s_ticket;
+  typedef ExecLds<T, KIND> Lds;
+  static_assert(offsetof(Lds, S) == 0, "transfers address LDS below 64 KB");
+  __shared__ __attribute__((aligned(1024))) Lds lds;   // the kernel's only LDS object
+  double* const S = lds.S;
+  double* const Xi = S + Lds::NS;
+  const Wait wt = {ctrl, limit, &lds.flag};
   // Control flow outside the task bodies is kept uniform across the
   // workgroup (values broadcast with readfirstlane, loops with uniform bounds
   // and predicated bodies): the compiler must never see a lane-divergent
   // region that straddles a barrier or the loop back-edge.
-  if (threadIdx.x == 0) s_ticket = atomicAdd(&ctrl->ticket, 1);
+  if (threadIdx.x == 0) lds.ticket = atomicAdd(&ctrl->ticket, 1);
   __syncthreads();
   ExecMat M = mats[0];
   for (;;) {
-    const int32_t t = __builtin_amdgcn_readfirstlane(s_ticket);
+    const int32_t t = __builtin_amdgcn_readfirstlane(lds.ticket);
     if (t >= total) break;
     int32_t mi = 0, lid = t;
     if (order) {
@@ -1912,7 +1927,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
     // ticket is void
     if (FACTOR && type == TK_POTRF && (w[0] & TF_CHAIN) != 0) {
       __syncthreads();
-      if (threadIdx.x == 0) s_ticket = atomicAdd(&ctrl->ticket, 1);
+      if (threadIdx.x == 0) lds.ticket = atomicAdd(&ctrl->ticket, 1);
       __syncthreads();
       continue;
     }
@@ -1922,7 +1937,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
     // its factor tiles are final then
     bool ok = true;
     if constexpr (BOTH) {
-      if (type >= TK_FUPD) ok = wait_below(cnt, MERGED_FDEP, ctrl, limit);
+      if (type >= TK_FUPD) ok = wait_below(cnt, MERGED_FDEP, wt);
     }
     // solve tasks other than FSUM wait for their predecessors themselves,
     // after reading their factor tiles; so do POTRF and TRSM (two-stage)
@@ -1931,7 +1946,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
     // wait until every predecessor has finished (Alg. 2 progress check);
     // wave 0 polls, then acquires for the workgroup (all its waves share
     // the CU's caches that the acquire invalidates)
-    if (!self_wait && ok) ok = wait_below(cnt, 1, ctrl, limit);
+    if (!self_wait && ok) ok = wait_below(cnt, 1, wt);
     if (M.trace) t_start = wall_clock64();
     // tasks on the pivot chain (diagonal factorization, panel solve, diagonal
     // solve steps) raise their waves' issue priority over the co-resident
@@ -1950,13 +1965,13 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
       if (type == TK_FSUM) {
         if (ok) task_fsum<T>(M, w, nrhs);
       } else {
-        t_start = task_solve_r<T, KIND>(M, w, nrhs, cnt, Xi, ctrl, limit, ok);
+        t_start = task_solve_r<T, KIND>(M, w, nrhs, cnt, Xi, wt, ok);
       }
     } else if (BOTH && type >= TK_FUPD) {
       if (type == TK_FSUM) {
         if (ok) task_fsum<T>(M, w, nrhs);
       } else {
-        t_start = task_solve_r<T, KIND>(M, w, nrhs, cnt, Xi, ctrl, limit, ok);
+        t_start = task_solve_r<T, KIND>(M, w, nrhs, cnt, Xi, wt, ok);
       }
     } else if (ok) {
       switch (type) {
@@ -1977,7 +1992,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
               load_task(M, lid2, w2);
               succ2 = load_words(M.succ + w2[5], w2[6] - w2[5]);
             }
-            t_start = t_trsm = task_trsm<T>(M, w, S, Xi, cnt, ctrl, limit, ok, pair, M.remaining + lid2,
+            t_start = t_trsm = task_trsm<T>(M, w, S, Xi, cnt, wt, ok, pair, M.remaining + lid2,
                                             M.tiles + (int64_t)w2[1] * (T * T), staged);
             if (!ok || !pair) break;
           }
@@ -1998,7 +2013,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
             }
             if (M.trace && l == 0) trace_task(M, lid1, t_claim, t_trsm, TK_TRSM, t);
           };
-          t_start = task_potrf<T>(M, w, S, Xi, cnt, ctrl, limit, ok, pair, staged, lead);
+          t_start = task_potrf<T>(M, w, S, Xi, cnt, wt, ok, pair, staged, lead);
           break;
         }
       }
@@ -2015,7 +2030,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
       // and the counters are re-armed by the last workgroup to leave
       if (threadIdx.x == 0) {
         atomicMin(M.info, 0ull);
-        s_ticket = next;
+        lds.ticket = next;
       }
       __syncthreads();
       continue;
@@ -2025,7 +2040,7 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
     // update); the workgroup-scope release only orders the notification
     // after the stores in the compiler
     __builtin_amdgcn_s_waitcnt(0);
-    if (threadIdx.x == 0) s_ticket = next;
+    if (threadIdx.x == 0) lds.ticket = next;
     __syncthreads();
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (threadIdx.x == 0) st_relaxed(cnt, w[7]);   // re-arm for the next launch
@@ -2039,16 +2054,15 @@ __global__ __launch_bounds__(NT, T == 32 ? 3 : 2) void exec_kernel(const ExecMat
   // also re-arms every progress counter of the launch (skipped tasks did not
   // re-arm theirs, and some were notified after being skipped).  Every
   // workgroup's notifications are complete before it counts itself out.
-  __shared__ int32_t s_last;
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   if (threadIdx.x == 0) {
     fence_release();
     const int e = atomicAdd(&ctrl->exited, 1);
-    s_last = e == (int)gridDim.x - 1;
+    lds.last = e == (int)gridDim.x - 1;
   }
   __syncthreads();
-  if (__builtin_amdgcn_readfirstlane(s_last)) {
+  if (__builtin_amdgcn_readfirstlane(lds.last)) {
     fence_acquire();
     if (__builtin_amdgcn_readfirstlane(ld_relaxed(&ctrl->abort)) != 0) {
       for (int32_t t = threadIdx.x; t < total; t += NT) {
