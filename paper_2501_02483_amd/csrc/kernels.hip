@@ -799,13 +799,15 @@ __device__ __forceinline__ void deferred_update(double (&D)[16], double (&a)[16]
   if constexpr (I < 14 - C) fnma_row<C + 2 + I>(D[C + 2 + I], D[C], D[C]);
   else fnma_row<2 * C + I - 13>(a[2 * C + I - 13], D[C], a[C]);
 }
+template <int C, int LO, int... I>
+__device__ __forceinline__ void deferred_updates(double (&D)[16], double (&a)[16], std::integer_sequence<int, I...>) {
+  (deferred_update<C, LO + I>(D, a), ...);
+}
 // one of six slots of them, kept in its place by the scheduling barrier
 template <int C, int SLOT>
 __device__ __forceinline__ void deferred_slot(double (&D)[16], double (&a)[16]) {
   constexpr int lo = deferred_count(C) * SLOT / 6, hi = deferred_count(C) * (SLOT + 1) / 6;
-  [&]<int... I>(std::integer_sequence<int, I...>) {
-    (deferred_update<C, lo + I>(D, a), ...);
-  }(std::make_integer_sequence<int, hi - lo>());
+  deferred_updates<C, lo>(D, a, std::make_integer_sequence<int, hi - lo>());
   __builtin_amdgcn_sched_barrier(0);
 }
 
