@@ -257,12 +257,12 @@ struct Ring {
 
 // 1 KB from base + voff (voff per lane) to LDS at lds + 16 lane.  No register
 // is written, so nothing can be overwritten by a transfer in flight; it
-// counts in vmcnt.
+// counts in vmcnt.  The LDS address goes in M0, which the compiler sets for
+// this operand (it then knows what M0 holds; a write inside the statement
+// would have to name a reserved register as clobbered); the wait state
+// between that write and the transfer is in the statement.
 __device__ __forceinline__ void lds_transfer(uint32_t lds, uint32_t voff, const char* base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds), "v"(voff), "s"(base)
-               : "memory", "m0");
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "{m0}"(lds), "v"(voff), "s"(base) : "memory");
 }
 
 // waits until at most `n` of this wave's newest transfers (n = 0, NI or 2 NI)

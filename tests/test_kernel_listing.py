@@ -29,6 +29,18 @@ def ir(tmp_path_factory):
     return _device(tmp_path_factory.mktemp("ir"), "kernels.ll", "-emit-llvm")[0]
 
 
+@pytest.fixture(scope="module")
+def listing(tmp_path_factory):
+    return _device(tmp_path_factory.mktemp("asm"), "kernels.s")
+
+
+def test_no_compiler_warnings(listing):
+    """A warning on the kernels is a defect to be seen: none of them are
+    expected (in particular none on what an asm statement may clobber)."""
+    found = [line for line in listing[1].splitlines() if "warning:" in line and "--hip-link" not in line]
+    assert not found, found[:5]
+
+
 def test_executor_lds_is_one_object(ir):
     """The operand ring's transfers address LDS below 64 KB and the ring is
     exactly that large at T = 64, so it has to start at LDS address 0: the
