@@ -14,7 +14,7 @@ import paper_2501_02483_amd as S
 UPD, PART, TREE, POTRF, TRSM, UPDB = 1, 2, 3, 4, 5, 6
 FUPD, FDIAG, BUPD, BDIAG, FPART, FSUM = 8, 9, 10, 11, 12, 13
 SWE, SW, SDIAG, TSUM = 16, 17, 18, 19
-TF_DIAG, TF_FIRST, TF_ACC, TF_SPLIT = 1 << 8, 1 << 9, 1 << 10, 1 << 11
+TF_DIAG, TF_FIRST, TF_ACC, TF_SPLIT, TF_CHAIN = 1 << 8, 1 << 9, 1 << 10, 1 << 11, 1 << 13
 SIG_TRANS = 1 << 30
 MERGED_FDEP, SUCC_FDEP = 1 << 16, 1 << 30
 SPLIT_W, SUCC_MID = 1 << 8, 1 << 29
@@ -68,7 +68,22 @@ def _order(tasks, succ, mode, rng):
         for t in range(n):
             for q in range(tasks[t, 5], tasks[t, 6]):
                 assert succ_edge(succ[q])[0] > t
-        return list(range(n))
+        # a chain pair's POTRF (the TRSM's first successor) runs right behind
+        # its TRSM, and no later ticket may be needed for it
+        out, rem = [], tasks[:, 7].copy()
+        for t in range(n):
+            flags = int(tasks[t, 0])
+            if flags & TF_CHAIN and (flags & 0xff) == POTRF:
+                continue
+            pair = [t, succ_edge(succ[tasks[t, 5]])[0]] if flags & TF_CHAIN else [t]
+            for x in pair:
+                assert rem[x] == 0, "task run before its predecessors"
+                out.append(x)
+                for q in range(tasks[x, 5], tasks[x, 6]):
+                    s, dec = succ_edge(succ[q])
+                    rem[s] -= dec
+        assert len(out) == n
+        return out
     rem = tasks[:, 7].copy()
     ready = [t for t in range(n) if rem[t] == 0]
     out = []

@@ -16,6 +16,14 @@
 // diagonal step waits for its early solve predecessors (weight 2^8, entries
 // with bit 29), reads its right-hand side block and the first fused
 // product's block, then waits for the last one.
+// A chain pair (TF_CHAIN on a TRSM and on the POTRF that is its first
+// successor) is run by the worker that drew the TRSM's ticket; the POTRF's
+// own ticket is void.  Before its last wait the TRSM stages the POTRF's tile
+// if that task's early predecessors finish first (its counter below 2: the
+// TRSM does not decrement it); the result reaches the POTRF in the worker's
+// own memory, and the TRSM's other successors are notified from inside the
+// POTRF, after its first panel.  Every task re-arms its counter for the next
+// launch; at the end all of them have to be armed.
 //
 // Input (binary, little-endian int32 header then arrays):
 //   T, ntiles, ntr, ntasks, nsucc, npairw (int32 words of the pair array),
@@ -23,11 +31,14 @@
 //   column-major doubles); for a merged DAG then nrhs (int32) and the
 //   right-hand side blocks (ntr blocks of T x nrhs column-major doubles).
 //   Output: the tiles, then (merged DAG) the solution blocks.
-// Usage: exec_race <in> <out> <threads> <seed> [drop_edge]
+// Usage: exec_race <in> <out> <threads> <seed> [drop_edge [fault]]
 //   out receives the factored tiles; drop_edge removes one successor entry
 //   (and its weight from the successor's counter) to plant a missing
-//   dependency; the task that lost the edge then starts 20 ms late, so that
-//   its former successor runs first in every interleaving.
+//   dependency; the task that lost the edge then starts 200 ms late, so that
+//   its former successor runs first in every interleaving.  -1: none; the
+//   entry of a chain pair itself cannot be removed.  fault plants a mistake
+//   in the pairs' protocol: 1, a TRSM notifies its successors before its
+//   result is stored; 2, the POTRF's tile is staged without a wait.
 #include <atomic>
 #include <chrono>
 #include <cmath>
@@ -43,7 +54,8 @@ namespace {
 
 constexpr int TK_UPD = 1, TK_PART = 2, TK_TREE = 3, TK_POTRF = 4, TK_TRSM = 5, TK_UPDB = 6;
 constexpr int TK_FUPD = 8, TK_FDIAG = 9, TK_BUPD = 10, TK_BDIAG = 11, TK_FPART = 12, TK_FSUM = 13;
-constexpr int TF_DIAG = 1 << 8, TF_FIRST = 1 << 9, TF_ACC = 1 << 10, TF_SPLIT = 1 << 11;
+constexpr int TF_DIAG = 1 << 8, TF_FIRST = 1 << 9, TF_ACC = 1 << 10, TF_SPLIT = 1 << 11,
+              TF_CHAIN = 1 << 13;
 constexpr int32_t W = 1 << 16, FDEP = 1 << 30, WMID = 1 << 8, MID = 1 << 29;
 
 struct Plan {
@@ -130,8 +142,123 @@ struct Exec {
     }
   }
   int32_t slow_task = -1;   // the source of a planted missing edge
+  int fault = 0;            // a planted mistake in the chain pairs' protocol
+  void slow(int32_t t) {
+    if (t == slow_task) std::this_thread::sleep_for(std::chrono::milliseconds(200));
+  }
+  // C -= sum of the fused products of task w
+  void fused(double* C, const int32_t* w, bool lower) {
+    for (int32_t q = w[3]; q < w[4]; q++) sub_prod(C, tile(p.pairs[2 * q]), tile(p.pairs[2 * q + 1]), lower);
+  }
+  // columns [c0, c1) of the Cholesky factor of the lower triangle, in place
+  bool cholesky(double* C, int c0, int c1) {
+    const int T = p.T;
+    for (int j = c0; j < c1; j++) {
+      double d = C[j + j * T];
+      for (int k = 0; k < j; k++) d -= C[j + k * T] * C[j + k * T];
+      if (!(d > 0.0)) { failed.store(true); return false; }
+      const double l = std::sqrt(d);
+      C[j + j * T] = l;
+      for (int i = j + 1; i < T; i++) {
+        double s = C[i + j * T];
+        for (int k = 0; k < j; k++) s -= C[i + k * T] * C[j + k * T];
+        C[i + j * T] = s / l;
+      }
+    }
+    return true;
+  }
+  // clears the upper triangle of a factor and inverts it into Li
+  void inverse(double* C, double* Li) {
+    const int T = p.T;
+    for (int c = 0; c < T; c++)
+      for (int r = 0; r < c; r++) C[r + c * T] = 0.0;
+    for (int c = 0; c < T; c++)
+      for (int r = 0; r < T; r++) {
+        if (r < c) { Li[r + c * T] = 0.0; continue; }
+        double s = r == c ? 1.0 : 0.0;
+        for (int k = c; k < r; k++) s -= C[r + k * T] * Li[k + c * T];
+        Li[r + c * T] = s / C[r + r * T];
+      }
+  }
+  // C = C Linv^T
+  void panel_solve(std::vector<double>& C, const int32_t* w) {
+    const int T = p.T;
+    const double* Li = linv.data() + (size_t)w[2] * T * T;
+    std::vector<double> out((size_t)T * T, 0.0);
+    for (int c = 0; c < T; c++)
+      for (int r = 0; r < T; r++) {
+        double s = 0.0;
+        for (int k = 0; k < T; k++) s += C[r + k * T] * Li[c + k * T];
+        out[r + c * T] = s;
+      }
+    C.swap(out);
+  }
+  // re-arms the counter of task t, then notifies its successors from the
+  // `first`-th on
+  void finish(int32_t t, int32_t first) {
+    const int32_t* w = &p.tasks[(size_t)t * 8];
+    cnt[t].store(w[7], std::memory_order_relaxed);
+    for (int32_t q = w[5] + first; q < w[6]; q++) {
+      const int32_t v = p.succ[q];
+      if (v == -1) continue;   // a planted missing edge
+      cnt[v & ~(FDEP | MID)].fetch_sub((v & FDEP) ? W : (v & MID) ? WMID : 1, std::memory_order_release);
+    }
+  }
+  // a TRSM and the POTRF that is its first successor
+  void run_pair(int32_t t, std::mt19937& rng) {
+    const int32_t* w = &p.tasks[(size_t)t * 8];
+    const int32_t y = p.succ[w[5]] & ~(FDEP | MID);
+    const int32_t* w2 = &p.tasks[(size_t)y * 8];
+    const int T = p.T;
+    const size_t bytes = (size_t)T * T * 8;
+    if ((w2[0] & 0xff) != TK_POTRF || !(w2[0] & TF_CHAIN) || !(w[0] & TF_SPLIT) || w2[4] - w2[3] != 1 ||
+        p.pairs[2 * w2[3]] != w[1] || p.pairs[2 * w2[3] + 1] != w[1]) {
+      std::fprintf(stderr, "exec_race: task %d is not a chain pair\n", t);
+      failed.store(true);
+      return;
+    }
+    std::vector<double> C((size_t)T * T), C2((size_t)T * T);
+    bool staged = fault == 2;
+    if (staged) std::memcpy(C2.data(), tile(w2[1]), bytes);
+    slow(t);
+    wait_below(t, W, rng);
+    std::memcpy(C.data(), tile(w[1]), bytes);
+    fused(C.data(), w, false);
+    // the POTRF's early predecessors or, failing that, the TRSM's late one
+    for (int spins = 0; !staged && !failed.load(std::memory_order_relaxed); spins++) {
+      if (cnt[y].load(std::memory_order_acquire) < 2) {
+        std::memcpy(C2.data(), tile(w2[1]), bytes);
+        staged = true;
+        break;
+      }
+      if (cnt[t].load(std::memory_order_acquire) < 1) break;
+      if (spins > 64) std::this_thread::sleep_for(std::chrono::microseconds(rng() % 20));
+      else std::this_thread::yield();
+    }
+    wait_below(t, 1, rng);
+    panel_solve(C, w);
+    if (fault == 1) {
+      finish(t, 1);
+      std::this_thread::sleep_for(std::chrono::milliseconds(5));
+    }
+    std::memcpy(tile(w[1]), C.data(), bytes);
+    slow(y);
+    if (!staged) {
+      wait_below(y, 2, rng);
+      std::memcpy(C2.data(), tile(w2[1]), bytes);
+    }
+    sub_prod(C2.data(), C.data(), C.data(), true);
+    if (!cholesky(C2.data(), 0, 16)) return;
+    if (fault != 1) finish(t, 1);
+    if (rng() % 8 == 0) std::this_thread::sleep_for(std::chrono::microseconds(rng() % 50));
+    if (!cholesky(C2.data(), 16, T)) return;
+    inverse(C2.data(), linv.data() + (size_t)w2[2] * T * T);
+    std::memcpy(tile(w2[1]), C2.data(), bytes);
+    if (rng() % 8 == 0) std::this_thread::sleep_for(std::chrono::microseconds(rng() % 50));
+    finish(y, 0);
+  }
   void run_task(int32_t t, std::mt19937& rng) {
-    if (t == slow_task) std::this_thread::sleep_for(std::chrono::milliseconds(20));
+    slow(t);
     const int32_t* w = &p.tasks[(size_t)t * 8];
     const int type = w[0] & 0xff, T = p.T;
     const bool split = (w[0] & TF_SPLIT) != 0;
@@ -139,44 +266,14 @@ struct Exec {
     if (type == TK_POTRF || type == TK_TRSM) {
       wait_below(t, split ? W : 1, rng);
       std::memcpy(C.data(), tile(w[1]), C.size() * 8);   // its own tile: an early input
-      if (type == TK_TRSM)                                  // fused products: early inputs
-        for (int32_t q = w[3]; q < w[4]; q++) sub_prod(C.data(), tile(p.pairs[2 * q]), tile(p.pairs[2 * q + 1]), false);
+      if (type == TK_TRSM) fused(C.data(), w, false);       // fused products: early inputs
       if (split) wait_below(t, 1, rng);
       if (type == TK_POTRF) {
-        for (int32_t q = w[3]; q < w[4]; q++) sub_prod(C.data(), tile(p.pairs[2 * q]), tile(p.pairs[2 * q + 1]), true);
-        // Cholesky of the lower triangle, then the inverse of the factor
-        for (int j = 0; j < T; j++) {
-          double d = C[j + j * T];
-          for (int k = 0; k < j; k++) d -= C[j + k * T] * C[j + k * T];
-          if (!(d > 0.0)) { failed.store(true); return; }
-          const double l = std::sqrt(d);
-          C[j + j * T] = l;
-          for (int i = j + 1; i < T; i++) {
-            double s = C[i + j * T];
-            for (int k = 0; k < j; k++) s -= C[i + k * T] * C[j + k * T];
-            C[i + j * T] = s / l;
-          }
-        }
-        for (int c = 0; c < T; c++)
-          for (int r = 0; r < c; r++) C[r + c * T] = 0.0;
-        double* Li = linv.data() + (size_t)w[2] * T * T;
-        for (int c = 0; c < T; c++)
-          for (int r = 0; r < T; r++) {
-            if (r < c) { Li[r + c * T] = 0.0; continue; }
-            double s = r == c ? 1.0 : 0.0;
-            for (int k = c; k < r; k++) s -= C[r + k * T] * Li[k + c * T];
-            Li[r + c * T] = s / C[r + r * T];
-          }
+        fused(C.data(), w, true);
+        if (!cholesky(C.data(), 0, T)) return;
+        inverse(C.data(), linv.data() + (size_t)w[2] * T * T);
       } else {
-        const double* Li = linv.data() + (size_t)w[2] * T * T;
-        std::vector<double> out((size_t)T * T, 0.0);
-        for (int c = 0; c < T; c++)
-          for (int r = 0; r < T; r++) {
-            double s = 0.0;
-            for (int k = 0; k < T; k++) s += C[r + k * T] * Li[c + k * T];
-            out[r + c * T] = s;
-          }
-        C.swap(out);
+        panel_solve(C, w);
       }
       std::memcpy(tile(w[1]), C.data(), C.size() * 8);
       return;
@@ -275,14 +372,15 @@ struct Exec {
     for (;;) {
       const int32_t t = ticket.fetch_add(1, std::memory_order_relaxed);
       if (t >= p.ntasks || failed.load(std::memory_order_relaxed)) break;
+      const int32_t flags = p.tasks[(size_t)t * 8];
+      if (flags & TF_CHAIN) {
+        // the POTRF of a pair runs behind its TRSM, its own ticket is void
+        if ((flags & 0xff) == TK_TRSM) run_pair(t, rng);
+        continue;
+      }
       run_task(t, rng);
       if (rng() % 8 == 0) std::this_thread::sleep_for(std::chrono::microseconds(rng() % 50));
-      const int32_t* w = &p.tasks[(size_t)t * 8];
-      for (int32_t q = w[5]; q < w[6]; q++) {
-        const int32_t v = p.succ[q];
-        if (v == -1) continue;   // a planted missing edge
-        cnt[v & ~(FDEP | MID)].fetch_sub((v & FDEP) ? W : (v & MID) ? WMID : 1, std::memory_order_release);
-      }
+      finish(t, 0);
     }
   }
 };
@@ -291,7 +389,7 @@ struct Exec {
 
 int main(int argc, char** argv) {
   if (argc < 5) {
-    std::fprintf(stderr, "usage: exec_race in out threads seed [drop_edge]\n");
+    std::fprintf(stderr, "usage: exec_race in out threads seed [drop_edge [fault]]\n");
     return 2;
   }
   Plan p;
@@ -299,19 +397,20 @@ int main(int argc, char** argv) {
     std::fprintf(stderr, "exec_race: cannot read %s\n", argv[1]);
     return 2;
   }
-  if (argc > 5) {
+  const int32_t drop = argc > 5 ? std::atoi(argv[5]) : -1;
+  if (drop >= 0) {
     // plant a missing dependency: the successor no longer waits for it
-    const int32_t e = std::atoi(argv[5]);
+    const int32_t e = drop;
     const int32_t v = p.succ[e];
+    for (int32_t t = 0; t < p.ntasks; t++)
+      if ((p.tasks[(size_t)t * 8] & (0xff | TF_CHAIN)) == (TK_TRSM | TF_CHAIN) && p.tasks[(size_t)t * 8 + 5] == e) return 2;
     p.tasks[(size_t)(v & ~(FDEP | MID)) * 8 + 7] -= (v & FDEP) ? W : (v & MID) ? WMID : 1;
     p.succ[e] = -1;
   }
   Exec ex(p);
-  if (argc > 5) {
-    const int32_t e = std::atoi(argv[5]);
-    for (int32_t t = 0; t < p.ntasks; t++)
-      if (p.tasks[(size_t)t * 8 + 5] <= e && e < p.tasks[(size_t)t * 8 + 6]) ex.slow_task = t;
-  }
+  for (int32_t t = 0; t < p.ntasks && drop >= 0; t++)
+    if (p.tasks[(size_t)t * 8 + 5] <= drop && drop < p.tasks[(size_t)t * 8 + 6]) ex.slow_task = t;
+  if (argc > 6) ex.fault = std::atoi(argv[6]);
   const int nth = std::atoi(argv[3]);
   const unsigned seed = (unsigned)std::atoi(argv[4]);
   std::vector<std::thread> th;
@@ -321,6 +420,11 @@ int main(int argc, char** argv) {
     std::fprintf(stderr, "exec_race: a task failed\n");
     return 3;
   }
+  for (int32_t t = 0; t < p.ntasks; t++)
+    if (ex.cnt[t].load() != p.tasks[(size_t)t * 8 + 7]) {
+      std::fprintf(stderr, "exec_race: the counter of task %d is not armed again\n", t);
+      return 4;
+    }
   FILE* f = std::fopen(argv[2], "wb");
   if (!f) return 2;
   bool ok = std::fwrite(p.tiles.data(), 8, p.tiles.size(), f) == p.tiles.size();

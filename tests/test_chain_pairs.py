@@ -54,3 +54,16 @@ def test_narrow_band_pairs_every_step():
         potrf = tasks[(tasks[:, 0] & 0xff) == E.POTRF]
         fused = potrf[:, 4] > potrf[:, 3]
         assert ((potrf[fused, 0] & TF_CHAIN) != 0).all() and fused.sum() >= len(potrf) - 2
+
+
+@pytest.mark.parametrize("tile", [32, 64])
+@pytest.mark.parametrize("sched_workers", [-1, 0, 16])
+def test_nd_plans_have_pairs(tile, sched_workers):
+    """The checks of test_pairs are not empty under adaptable ND."""
+    p = I.make_pattern(2300, 24, [20, 150, 260], seg=500)
+    sym = S.Symbolic.from_pattern(p, tile=tile, sched_workers=sched_workers, ordering=S.STILES_ORDER_ADAPTABLE_ND,
+                                  nd_parts=3)
+    assert sym.info.nd_parts == 3
+    for name in ("ftask", "mtask"):
+        tasks = S.stiles_symbolic_export(sym.handle, name).reshape(-1, 8)
+        assert ((tasks[:, 0] & (0xff | TF_CHAIN)) == (E.TRSM | TF_CHAIN)).sum() >= 5
