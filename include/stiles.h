@@ -112,10 +112,11 @@ typedef struct stiles_opts {
                              -- chain steps against executed flops -- wins)       */
   int32_t sched_workers;  /* ticket order of the task DAGs: the start order of a list
                              schedule (longest remaining path first) on this many
-                             workgroups (0 = 512, a full MI355X launch), used for a DAG
-                             whose critical path is at least half its work per
-                             workgroup and for batches; otherwise, and with -1, the
-                             order by earliest start with unlimited workgroups.  Only
+                             workgroups (0 = 512: a full MI355X launch at T = 64; at
+                             T = 32 a launch has 768), used for a DAG whose critical
+                             path is at least half its work per workgroup and for
+                             batches; otherwise, and with -1, the order by earliest
+                             start with unlimited workgroups.  Only
                              the speed depends on it: every order gives bitwise the
                              same results                                            */
   int32_t ublock;         /* 2 x 2 blocked tile updates (two tile rows of two adjacent

@@ -129,7 +129,8 @@ void chain_pairs(TaskBuilder& tb, std::vector<int32_t>& order) {
 }
 
 // workgroups of the list schedule: a full-GPU executor launch has two per CU
-// on 256 CUs; -1 (option) = unbounded earliest-start order
+// on 256 CUs at T = 64 (three at T = 32, where the same default is kept: it
+// only sets the order); -1 (option) = unbounded earliest-start order
 int sched_workers(const stiles_opts& o) { return o.sched_workers == 0 ? 512 : o.sched_workers < 0 ? 0 : o.sched_workers; }
 
 // Static schedule: earliest start in an unbounded-resource model (hop latency
@@ -190,11 +191,17 @@ void schedule(TaskBuilder& tb, std::vector<int32_t>& tasks_out, std::vector<int3
     order = list_order(nt, tb.cost.data(), sptr.data(), sflat.data(), npred.data(), bl.data(), workers, hop);
   }
   // chain pairs where the pivot chain bounds the run: its length is several
-  // times the work per workgroup.  (Measured against no pairs, by work per
-  // workgroup / critical path: up to 0.02, n = 1,000 to 20,000 in natural or
-  // AMD order, 2.5 to 7.5 % faster; 0.88, 1.9 and 4.2, n = 96,000 to 500,000
-  // under adaptable ND, about 1 % slower: a TRSM's other successors hear of
-  // it later, and another workgroup would have staged the POTRF's tile.)
+  // times the work per workgroup (of 512, whatever the launch is capped to).
+  // Measured against no pairs, by work per workgroup / critical path, factor
+  // and merged launch: T = 64, up to 0.05 0.2 to 3 % faster in natural order
+  // with wide bands and 2.5 to 7.5 % with narrow ones, 0.07 to 0.25 0.6 to
+  // 5 %, 0.29 1.3 to 2 %, 0.38 to 0.69 0.4 to 1 %; 0.88, 1.9 and 4.2 (n =
+  // 96,000 to 500,000) about 1 % slower: a TRSM's other successors hear of it
+  // later, and another workgroup would have staged the POTRF's tile.  T = 32:
+  // up to 0.07 6 to 15 %, 0.12 to 0.44 1.7 to 6 %, 0.6 to 0.77 0.3 to 1.4 %
+  // faster.  Launches capped to 8, 32 and 128 workgroups: between 0.3 %
+  // slower and 4 % faster (13 % at T = 32).  So the line loses at most a few
+  // percent between 0.25 and 0.7 and costs nothing below.
   if (tot / 512.0 < 0.25 * blmax) chain_pairs(tb, order);
   std::vector<int32_t> newid(nt);
   for (int i = 0; i < nt; i++) newid[order[i]] = i;
@@ -960,11 +967,17 @@ namespace {
 // chain-based choice P0 (see nd_plan) and two smaller counts are analyzed
 // in full, and the one with the least estimated time is kept.  The estimate
 // is the larger of the plan's chain (tile steps) times a step's duration
-// and its executed flops over the executor's executed rate (measured on
-// MI355X: a pivot step about 50 us at T = 64, 30 us at T = 32; about 34 and
-// 17.5 TFLOP/s executed): long narrow bands are bound by their chain, for
-// which P0 is made, wide bands by the fill that every interior partition
-// adds, which fewer partitions save.  Small matrices keep P0.
+// and its executed flops over the executor's executed rate: long narrow bands
+// are bound by their chain, for which P0 is made, wide bands by the fill that
+// every interior partition adds, which fewer partitions save.  Small matrices
+// keep P0.  The constants (a pivot step of 50 us at T = 64, 30 us at T = 32; 34
+// and 17.5 TFLOP/s) are those of earlier kernels.  At T = 64 the current ones
+// take 12.4 us a step alone and about 15 under load and execute 41 to 58
+// TFLOP/s, which would choose fewer partitions: the factorization gains (n =
+// 500,000: 8 instead of 17, 57.2 -> 53.5 ms with its solve; spatio-temporal
+// input: 3 instead of 5, 17.7 -> 16.5 ms), but every solve of its own gets
+// longer (6.5 -> 9.6 ms, 3.8 -> 4.8 ms) and the permutation changes, so the
+// counts stay.
 template <typename Fn>
 stiles_status analyze_auto_parts(const stiles_opts* opts, Fn analyze_with, stiles_symbolic** out) {
   stiles_status st = analyze_with(opts, out);

@@ -237,10 +237,13 @@ __device__ __forceinline__ int wait_first(int32_t* a, int32_t ba, int32_t* b, in
 // Tile pairs stream through LDS in stages of KS columns of X and of Y (a
 // column range of a column-major tile is contiguous), written by the memory
 // system itself (global_load_lds: no staging registers and no LDS store
-// instructions).  Two or more stages are in flight while one is multiplied;
-// one barrier per stage, after its first step so that the matrix cores work
+// instructions).  With NST slots the next NST - 2 stages have been issued
+// when a stage's products begin, and one more follows during them; one
+// barrier per stage, after its first step so that the matrix cores work
 // meanwhile, says both that the next stage has arrived and that the slot of
-// the previous one is free.  Tiles staged whole through registers gave the
+// the previous one is free.  At T = 64 (four slots) it leaves the stage after
+// the next in flight; at T = 32 (three, whole operand tiles) the next stage
+// is the only one, and the barrier waits for it.  Tiles staged whole through registers gave the
 // matrix cores nothing to do while a pair was stored to LDS and the next
 // one's 16 loads went out; 512 workgroups of 12-product tasks on tiles in
 // L2: FP64 49 -> 58 TFLOP/s, FP32 96 -> 105; on tiles in HBM both are bound by
@@ -1220,7 +1223,8 @@ __device__ __forceinline__ uint64_t task_solve_r(const ExecMat& M, const Task& w
 
 // Y_m -= Q_a + ... + Q_(b-1): the partial products of a long row, summed in
 // a fixed order (so the result does not depend on the schedule): four running
-// sums, slot q in sum (q - a) mod 4.  The task is on the chain of the
+// sums, slot q in sum (q - a) mod 4, the last (b - a) mod 4 slots all in the
+// first.  The task is on the chain of the
 // separators' steps and waits for memory only: eight slots are in flight for
 // every pair of elements, and all pairs of a lane at once (four slots of one
 // element at a time: 9.4 us a task, now 4.2; the solve above 2.12 -> 1.96 ms).
