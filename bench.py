@@ -24,7 +24,7 @@ ooc (out-of-core factorization of the variable-bandwidth matrix by band
 segments, host values in and host factor out), banded (host context: LAPACK
 band Cholesky plus the arrow on the host cores, beside the GPU's FP64
 factorization of the same constant-width matrices), copycal (a device copy
-of known size, to calibrate the HBM byte counters).
+of known size, to calibrate the byte counters past L2).
 """
 import argparse
 import json
@@ -62,9 +62,9 @@ def to_device_cols(B):
 
 
 def measured_traffic(workload, tile):
-    """HBM bytes per factorization launch from the committed rocprofv3 --pmc
-    summary (FETCH_SIZE and WRITE_SIZE, scaled by a copy of known size), or
-    None when there is none for this workload or the kernel source changed
+    """Bytes past L2 (HBM and memory-side cache) per factorization launch from
+    the committed rocprofv3 --pmc summary (FETCH_SIZE and WRITE_SIZE, scaled
+    by a copy of known size), or None when there is none for this workload or the kernel source changed
     since the counters were taken."""
     import hashlib
     root = os.path.dirname(os.path.abspath(__file__))
@@ -878,7 +878,7 @@ def bench_ooc(args):
 
 
 def bench_copycal(args):
-    """Plain device copy of a known size (counter calibration for HBM traffic)."""
+    """Plain device copy of a known size (counter calibration for the traffic past L2)."""
     import torch
     nbytes = 1 << 30
     a = torch.empty(nbytes // 8, dtype=torch.float64, device="cuda").fill_(1.0)
